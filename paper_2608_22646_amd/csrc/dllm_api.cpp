@@ -73,7 +73,7 @@ namespace {
 // ---------------------------------------------------------------- layout
 struct Layout {
   size_t h, a_attn, q, k, vt, attn, a_mlp, u, hb, cosb, sinb;
-  size_t raw, gate, up, logits;                  // fp32 path
+  size_t logits;                                 // fp32 path
   size_t part_m, part_s, part_i, ticket, hbf;    // bf16 head
   size_t splitk;                                 // bf16 split-K GEMM partials
   size_t attn_part, attn_ticket;                 // bf16 key-split attention states and tickets
@@ -109,11 +109,7 @@ Layout make_layout(const dllm_model_cfg& c, int B, int L, int rows) {
   o.sinb = take((size_t)L * hd / 2 * 4);
   o.all_done = take(4);
   o.err = take(4);
-  if (c.dtype == DLLM_F32) {
-    o.raw = take(M * (c.n_heads + 2 * c.n_kv_heads) * hd * 4);
-    o.gate = take(M * F * 4);
-    o.up = take(M * F * 4);
-  } else {
+  if (c.dtype != DLLM_F32) {
     o.ticket = take(4);
     o.hbf = take((size_t)HEAD_FRAG_ROWS * d * 2);
     o.attn_ticket = take((size_t)B * c.n_heads * 4);
@@ -374,53 +370,90 @@ void run_layer_bf16(const dllm_model* m, int layer, int part, int B, int L, void
   }
 }
 
+// RMSNorm of rows (b, row0 + i), i < rows, of h into g.normed and the GEMM g on
+// them: one launch where the GEMM takes the norm along, else two.
+void norm_gemm_f32(const dllm_model* m, GemmF32 g, const float* h, const float* gain, float* normed, int B, int rows,
+                   int L, int row0, hipStream_t s, int kind) {
+  g.M = B * rows;
+  g.K = m->cfg.d_model;
+  g.A = h;
+  g.gain = gain;
+  g.normed = normed;
+  g.eps = m->cfg.rms_eps;
+  if (gemm_f32_fuses_norm(g)) {
+    g.rows = rows;
+    g.Ls = L;
+    g.r0 = row0;
+  } else {
+    ProfScope p(m, PK_NORM, s);
+    launch_rmsnorm(h, gain, normed, 0, B, rows, L, row0, m->cfg.d_model, m->cfg.rms_eps, s);
+    g.A = normed;
+    g.gain = nullptr;
+    g.normed = nullptr;
+  }
+  ProfScope p(m, kind, s);
+  launch_gemm_f32(g, s);
+}
+
 void run_layer_f32(const dllm_model* m, int layer, int part, int B, int L, void* ws, const Layout& lay,
                    hipStream_t s, const LayerRows* rows = nullptr) {
   const auto& c = m->cfg;
   const int base = 1 + 9 * layer;
   const int Lq = rows ? rows->Lq : L, pos0 = rows ? rows->pos0 : 0;
   const int M = B * Lq, d = c.d_model, hd = c.head_dim, F = c.d_ff;
-  float* kk = rows && rows->k ? static_cast<float*>(rows->k) : at<float>(ws, lay.k);
-  float* vv = rows && rows->vt ? static_cast<float*>(rows->vt) : at<float>(ws, lay.vt);
-  const int nq = c.n_heads * hd, nkv = c.n_kv_heads * hd, nraw = nq + 2 * nkv;
   float* h = at<float>(ws, lay.h);
   if (part == 0 || part == 2) {
-    float* a = at<float>(ws, lay.a_attn);
-    float* raw = at<float>(ws, lay.raw);
-    {
-      ProfScope p(m, PK_NORM, s);
-      launch_rmsnorm(h, W(m, base + 0), a, 0, B, Lq, Lq, 0, d, c.rms_eps, s);
-    }
-    {
-      ProfScope p(m, PK_QKV, s);
-      launch_gemm_f32(a, Wf(m, base + 1), raw, M, nq, d, nraw, false, s);
-      launch_gemm_f32(a, Wf(m, base + 2), raw + nq, M, nkv, d, nraw, false, s);
-      launch_gemm_f32(a, Wf(m, base + 3), raw + nq + nkv, M, nkv, d, nraw, false, s);
-    }
-    launch_rope_split_f32(raw, at<float>(ws, lay.cosb), at<float>(ws, lay.sinb), at<float>(ws, lay.q), kk, vv, B,
-                          Lq, L, pos0, c.n_heads, c.n_kv_heads, hd, s);
+    GemmF32 g{};
+    g.epi = F32_QKV;
+    g.N = (c.n_heads + 2 * c.n_kv_heads) * hd;
+    g.W0 = Wf(m, base + 1);
+    g.W1 = Wf(m, base + 2);
+    g.W2 = Wf(m, base + 3);
+    g.q = at<float>(ws, lay.q);
+    g.k = rows && rows->k ? static_cast<float*>(rows->k) : at<float>(ws, lay.k);
+    g.vt = rows && rows->vt ? static_cast<float*>(rows->vt) : at<float>(ws, lay.vt);
+    g.cosb = at<float>(ws, lay.cosb);
+    g.sinb = at<float>(ws, lay.sinb);
+    g.Lq = Lq;
+    g.L = L;
+    g.pos0 = pos0;
+    g.Hq = c.n_heads;
+    g.Hkv = c.n_kv_heads;
+    g.hd = hd;
+    norm_gemm_f32(m, g, h, Wf(m, base + 0), at<float>(ws, lay.a_attn), B, Lq, Lq, 0, s, PK_QKV);
     {
       ProfScope p(m, PK_ATTN, s);
-      launch_attn_f32(at<float>(ws, lay.q), kk, vv, at<float>(ws, lay.attn), B, Lq, L, c.n_heads, c.n_kv_heads, hd,
-                      s);
+      launch_attn_f32(g.q, g.k, g.vt, at<float>(ws, lay.attn), B, Lq, L, c.n_heads, c.n_kv_heads, hd, s);
     }
+    GemmF32 o{};
+    o.epi = F32_RESID;
+    o.M = M;
+    o.N = d;
+    o.K = c.n_heads * hd;
+    o.A = at<float>(ws, lay.attn);
+    o.W0 = Wf(m, base + 4);
+    o.C = h;
     ProfScope p(m, PK_OPROJ, s);
-    launch_gemm_f32(at<float>(ws, lay.attn), Wf(m, base + 4), h, M, d, nq, d, true, s);
+    launch_gemm_f32(o, s);
   }
   if (part == 1 || part == 2) {
-    float* a = at<float>(ws, lay.a_mlp);
-    {
-      ProfScope p(m, PK_NORM, s);
-      launch_rmsnorm(h, W(m, base + 5), a, 0, B, Lq, Lq, 0, d, c.rms_eps, s);
-    }
-    {
-      ProfScope p(m, PK_GATEUP, s);
-      launch_gemm_f32(a, Wf(m, base + 6), at<float>(ws, lay.gate), M, F, d, F, false, s);
-      launch_gemm_f32(a, Wf(m, base + 7), at<float>(ws, lay.up), M, F, d, F, false, s);
-    }
-    launch_swiglu_f32(at<float>(ws, lay.gate), at<float>(ws, lay.up), at<float>(ws, lay.u), (long)M * F, s);
+    GemmF32 g{};
+    g.epi = F32_SWIGLU;
+    g.N = F;
+    g.W0 = Wf(m, base + 6);
+    g.W1 = Wf(m, base + 7);
+    g.C = at<float>(ws, lay.u);
+    norm_gemm_f32(m, g, h, Wf(m, base + 5), at<float>(ws, lay.a_mlp), B, Lq, Lq, 0, s, PK_GATEUP);
+    GemmF32 dn{};
+    dn.epi = F32_RESID;
+    dn.M = M;
+    dn.N = d;
+    dn.K = F;
+    dn.A = at<float>(ws, lay.u);
+    dn.W0 = Wf(m, base + 8);
+    dn.C = h;
     ProfScope p(m, PK_DOWN, s);
-    launch_gemm_f32(at<float>(ws, lay.u), Wf(m, base + 8), h, M, d, F, d, true, s);
+    launch_gemm_f32(dn, s);
   }
 }
 
@@ -474,22 +507,22 @@ void run_head_bufs(const dllm_model* m, int B, int L, int row0, int rows, float*
   // bf16: up to HEAD_FRAG_ROWS head rows also go to an MFMA-operand-order copy
   // for the streaming head kernel
   bf16_t* hbf = c.dtype == DLLM_BF16 && R <= HEAD_FRAG_ROWS ? hb.hbf : nullptr;
-  {
-    ProfScope p(m, PK_NORM, s);
-    // the head kernel's ticket is zeroed here (no memset node in a captured step)
-    if (c.dtype == DLLM_BF16)
+  if (c.dtype == DLLM_F32) {
+    GemmF32 g{};
+    g.epi = F32_STORE;
+    g.N = c.vocab;
+    g.W0 = Wf(m, 2 + 9 * nl);
+    g.C = logits ? logits : hb.logits;
+    norm_gemm_f32(m, g, hb.h, Wf(m, 1 + 9 * nl), static_cast<float*>(hb.hb), B, rows, L, row0, s, PK_HEAD);
+    launch_vocab_reduce_f32(g.C, R, c.vocab, c.mask_id, conf, argmax, s);
+  } else {
+    {
+      ProfScope p(m, PK_NORM, s);
+      // the head kernel's ticket is zeroed here (no memset node in a captured step)
       launch_rmsnorm_head(hb.h, pend, static_cast<const bf16_t*>(W(m, 1 + 9 * nl)), static_cast<bf16_t*>(hb.hb), hbf,
                           B, rows, L, row0, c.d_model, c.rms_eps, hb.ticket, s);
-    else
-      launch_rmsnorm(hb.h, W(m, 1 + 9 * nl), hb.hb, c.dtype, B, rows, L, row0, c.d_model, c.rms_eps, s);
-  }
-  ProfScope p(m, PK_HEAD, s);
-  if (c.dtype == DLLM_F32) {
-    float* lg = logits ? logits : hb.logits;
-    launch_gemm_f32(static_cast<const float*>(hb.hb), Wf(m, 2 + 9 * nl), lg, R, c.vocab, c.d_model, c.vocab, false,
-                    s);
-    launch_vocab_reduce_f32(lg, R, c.vocab, c.mask_id, conf, argmax, s);
-  } else {
+    }
+    ProfScope p(m, PK_HEAD, s);
     HeadArgs a{};
     a.hb = static_cast<const bf16_t*>(hb.hb);
     a.hbf = hbf;

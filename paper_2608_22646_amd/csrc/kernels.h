@@ -26,16 +26,29 @@ void launch_state_init(const int32_t* prompt, int32_t* x, int32_t* commit_step, 
                        int* err, hipStream_t s);
 
 // ---- fp32 path (k_f32.hip) -------------------------------------------------
-// C[M, N] (+)= A[M, K] W[N, K]^T, all float32 row-major, C row stride ldc.
-void launch_gemm_f32(const float* A, const float* W, float* C, int M, int N, int K, int ldc, bool accumulate,
-                     hipStream_t s);
-// Split raw projections [B*Lq, (Hq + 2 Hkv) hd] of the rows at positions pos0 ..
-// pos0 + Lq - 1 of each sequence into q [B, Hq, Lq, hd] and k [B, Hkv, L, hd]
-// (RoPE applied) and v^T [B, Hkv, hd, L] (k, v^T at those positions).
-void launch_rope_split_f32(const float* raw, const float* cosb, const float* sinb, float* q, float* k,
-                           float* vt, int B, int Lq, int L, int pos0, int Hq, int Hkv, int hd, hipStream_t s);
-// out[i] = silu(gate[i]) * up[i]
-void launch_swiglu_f32(const float* gate, const float* up, float* out, long n, hipStream_t s);
+// C = A W^T of an fp32 model (all float32 row-major, float64 accumulation), by epi:
+//   F32_QKV    W0/W1/W2 = wq/wk/wv; RoPE on q and k; row m = b Lq + i holds
+//              position pos0 + i of sequence b: q [B, Hq, Lq, hd], k [B, Hkv, L,
+//              hd] and v^T [B, Hkv, hd, L] (N = the three tensors' rows)
+//   F32_SWIGLU W0/W1 = gate/up [N, K]: C[M, N] = silu(gate) * up
+//   F32_RESID  C[M, N] += A W0^T          F32_STORE  C[M, N] = A W0^T
+// With rows > 0 row m of A is row (m / rows) Ls + r0 + m % rows.  With gain set
+// (gemm_f32_fuses_norm; not F32_RESID) the rows of A are RMS-normalised first,
+// and the normed rows [M, K] stored at `normed`.
+enum { F32_QKV = 0, F32_SWIGLU = 1, F32_RESID = 2, F32_STORE = 3 };
+struct GemmF32 {
+  int epi;
+  int M, N, K;
+  const float* A;
+  const float* W0; const float* W1; const float* W2;
+  float* C;
+  int rows, Ls, r0;
+  const float* gain; float* normed; float eps;
+  float* q; float* k; float* vt; const float* cosb; const float* sinb;
+  int Lq, L, pos0, Hq, Hkv, hd;
+};
+bool gemm_f32_fuses_norm(const GemmF32& g);
+void launch_gemm_f32(GemmF32 g, hipStream_t s);
 // Non-causal attention, float32, of Lq queries per sequence (q [B, Hq, Lq, hd])
 // over L keys (k [B, Hkv, L, hd], v^T [B, Hkv, hd, L]): out[b*Lq + l, h*hd + j].
 void launch_attn_f32(const float* q, const float* k, const float* vt, float* out, int B, int Lq, int L, int Hq,

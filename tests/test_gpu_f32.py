@@ -1,0 +1,75 @@
+"""float32 models at the edges of the matrix-core tiles, against the float64 oracle.
+
+The tile edges: rows and columns that are no multiple of 16, reduction lengths
+that are no multiple of 16 (scalar operand loads), widths beyond the fused
+norm's 512, both head dimensions, grouped heads, and enough rows for every tile
+height (16 rows on eight or four waves, 32 rows).
+"""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import forward as of
+from oracle import vocab as ov
+from paper_2608_22646_amd import binding as B
+from paper_2608_22646_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def config(d, heads, kv, hd, ff, vocab):
+    return synth.ModelConfig("f32-edge", n_layers=2, d_model=d, n_heads=heads, n_kv_heads=kv, head_dim=hd, d_ff=ff,
+                             vocab=vocab, rope_base=10000.0, dtype="f32", lm_head_std=5.0 / math.sqrt(d),
+                             norm_gain_std=0.2)
+
+
+@pytest.mark.parametrize("Bn,L,row0,rows,shape", [
+    (1, 17, 1, 9, (250, 4, 2, 64, 333, 777)),      # scalar loads, every dimension ragged
+    (1, 1, 0, 1, (256, 2, 1, 128, 88, 100)),       # a single position
+    (3, 45, 7, 32, (528, 4, 2, 128, 352, 1031)),   # norm in its own launch
+    (2, 301, 200, 33, (512, 6, 3, 64, 720, 2048)), # widest fused norm
+    (4, 530, 3, 64, (256, 4, 4, 64, 704, 4099)),   # 32-row tiles
+])
+def test_forward_matches_float64(gpu_lib, Bn, L, row0, rows, shape):
+    cfg = config(*shape)
+    w = synth.make_weights(cfg, "cpu")
+    model = B.Model(cfg, [t.cuda() for t in w])
+    x = synth.make_ints((Bn, L), 5, 0, cfg.vocab)
+    conf, arg, lg = model.forward(x.cuda(), row0, rows, logits=True)
+    ref = of.forward(cfg, [t.numpy().astype(np.float64) for t in w], x.numpy(), rows=np.arange(row0, row0 + rows))
+    got = lg.cpu().numpy().astype(np.float64)
+    # a stored float32 value is the rounding of a float64 sum; two layers of such
+    # roundings (2^-24 relative each, ~20 per path) on logits of spread 5
+    assert np.abs(got - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max() / 5)
+    c_ref, a_ref = ov.confidence_argmax(got, cfg.mask_id)
+    np.testing.assert_allclose(conf.cpu().numpy(), c_ref, rtol=2e-6)
+    np.testing.assert_array_equal(arg.cpu().numpy(), a_ref)
+
+
+def test_scores_of_minus_infinity_drop_out(gpu_lib):
+    """Keys whose scores are -inf take no part, also where whole 16-key tiles are of that kind."""
+    cfg = config(256, 4, 4, 64, 64, 64)
+    model = B.Model(cfg, [t.cuda() for t in synth.make_weights(cfg, "cpu")])
+    L, pos, dead = 64, 40, 32
+    ws, kv, lay = model.workspace(1, L, 1), model.kv_cache(1, L), model.layout(1, L, 1)
+    n = cfg.n_kv_heads * L * cfg.head_dim
+    K = kv[:4 * n].view(torch.float32).view(cfg.n_kv_heads, L, cfg.head_dim)
+    V = kv[4 * n:8 * n].view(torch.float32).view(cfg.n_kv_heads, cfg.head_dim, L)
+    kv.zero_()
+    K.copy_(synth.make_normal(K.shape, 7))
+    V.copy_(synth.make_normal(V.shape, 8))
+    x = synth.make_ints((1, L), 3, 0, cfg.vocab).cuda()
+    q = ws[lay.q:lay.q + 4 * 256].view(torch.float32).view(4, 1, 64)
+    for _ in range(2):  # the first pass only yields q; its signs then make every dead key's score -inf
+        model.embed_rows(x, pos, 1, ws)
+        model.layer_kv(0, 0, 1, L, pos, 1, kv, ws)
+        K[:, :dead] = torch.where(q > 0, -math.inf, math.inf).expand(-1, dead, -1)
+    got = ws[lay.attn:lay.attn + 4 * 256].view(torch.float32).double().cpu().numpy().reshape(4, 64)
+    qd = q.double().cpu().numpy()[:, 0]
+    kk, vv = K.double().cpu().numpy()[:, dead:], V.double().cpu().numpy()[:, :, dead:]
+    sc = (qd[:, None] * kk).sum(-1) / 8.0
+    p = np.exp(sc - sc.max(-1, keepdims=True))
+    ref = ((p / p.sum(-1, keepdims=True))[:, None] * vv).sum(-1)
+    np.testing.assert_allclose(got, ref, rtol=1e-6, atol=1e-6)
