@@ -322,7 +322,7 @@ int dllm_step(const dllm_model* model, const dllm_cai_params* params, dllm_state
  * (Section 4.3), running dllm_step until each block finishes.  Waits for the
  * stream once per step (the block-finished flag) and returns after the last
  * step, or after the first step whose error word is set (the errors of
- * dllm_step).  The RoPE tables are built once, before the first step.
+ * dllm_step).  The RoPE tables are built once, in the first step.
  * forwards_host: optional host int32 [G/bl], forwards run per block.
  * conf_trace / argmax_trace: optional device [G/bl, T, B, bl] records of every
  * step's predictions (entries of steps not run are left untouched).

@@ -227,19 +227,15 @@ void check_kv(const dllm_model* m, int B, int L, const void* kv, size_t bytes) {
 
 // ---------------------------------------------------------------- forward pieces
 // h[b rows + i] = embedding of x[b, row0 + i] (rows = L, row0 = 0: every
-// position); with rope set, first the RoPE tables for all L positions, which
-// also clears the error word (a decode builds them once, before its first
-// step, after clearing the word in the state initialisation; each commit
-// clears it after reporting).
+// position), and the error word for these ids; with rope set also the RoPE
+// tables for all L positions (a decode builds them once, in its first step).
 void run_embed(const dllm_model* m, const int32_t* x, int B, int L, int row0, int rows, void* ws, const Layout& lay,
                hipStream_t s, bool rope = true) {
   const auto& c = m->cfg;
-  if (rope)
-    launch_rope_table(at<float>(ws, lay.cosb), at<float>(ws, lay.sinb), L, c.head_dim, c.rope_base,
-                      at<int>(ws, lay.err), s);
+  const RopeTable table{at<float>(ws, lay.cosb), at<float>(ws, lay.sinb), c.head_dim, c.rope_base};
   const bool bf = c.dtype == DLLM_BF16;
   launch_embed(x, W(m, 0), c.dtype, at<float>(ws, lay.h), B, rows, L, row0, c.d_model, c.vocab, at<int>(ws, lay.err),
-               s, bf ? at<int>(ws, lay.attn_ticket) : nullptr, bf ? B * c.n_heads : 0);
+               s, bf ? at<int>(ws, lay.attn_ticket) : nullptr, bf ? B * c.n_heads : 0, rope ? &table : nullptr);
 }
 
 void gemm_bf16(const dllm_model* m, GemmArgs g, void* ws, const Layout& lay, hipStream_t s, int kind,
@@ -1172,11 +1168,6 @@ void generate_impl(const dllm_model* m, const dllm_cai_params* p, const int32_t*
   const int bl = p->block_len, nb = G / bl, T = steps_T(p);
   launch_state_init(prompt, st->x, st->commit_step, st->reason, st->s, st->budget, st->ell, st->done, B, P, G,
                     m->cfg.mask_id, at<int>(ws, lay.err), s);
-  {  // positions are fixed for the whole decode: one RoPE table
-    ProfScope pr(m, PK_NORM, s);
-    launch_rope_table(at<float>(ws, lay.cosb), at<float>(ws, lay.sinb), P + G, m->cfg.head_dim, m->cfg.rope_base,
-                      nullptr, s);
-  }
   int total = 0;
   for (int blk = 0; blk < nb; ++blk) {
     int n = 0;
@@ -1185,7 +1176,7 @@ void generate_impl(const dllm_model* m, const dllm_cai_params* p, const int32_t*
       int32_t* at_ = argmax_trace ? argmax_trace + ((size_t)blk * T + t) * B * bl : nullptr;
       const int seq = next_seq(m);
       step_impl(m, p, st, B, P, G, blk, t, ct, at_, ws, lay, s, kv, refresh_every == 0 || t % refresh_every == 0,
-                false, seq);
+                blk == 0 && t == 0, seq);  // positions are fixed: one RoPE table for the whole decode
       ++n;
       const int flag = wait_step(m, s, seq);
       raise_step_errors(flag);

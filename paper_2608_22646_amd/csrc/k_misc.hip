@@ -16,59 +16,113 @@ int device_cu_count() {
   return cus;
 }
 
-// One 256-thread block per row; every thread converts a strided set of columns.
-// Row m = b rows + i gathers token x[b, row0 + i]; an id outside [0, V) is
-// never used as an address: the row is zero and the error word says so.
-template <typename T>
-__global__ void __launch_bounds__(256) embed_kernel(const int32_t* __restrict__ x, const T* __restrict__ E,
-                                                    float* __restrict__ h, int rows, int L, int row0, int d, int V,
-                                                    int* __restrict__ err, int* __restrict__ zero, int nzero) {
-  const int m = blockIdx.x, b = m / rows, i = m - b * rows;
-  if (m == 0)
-    for (int z = threadIdx.x; z < nzero; z += 256) zero[z] = 0;
-  const int tok = x[(size_t)b * L + row0 + i];
-  const bool ok = tok >= 0 && tok < V;
-  const size_t src = (size_t)(ok ? tok : 0) * d;
-  float* dst = h + (size_t)m * d;
-  for (int c = threadIdx.x; c < d; c += 256) dst[c] = ok ? Act<T>::load(E, src + c) : 0.f;
-  if (!ok && threadIdx.x == 0 && err) atomicOr(err, (int)ERR_TOKEN_RANGE);
+// Four consecutive elements c4 of a row (16-byte aligned float, 8-byte bf16).
+template <typename T> struct Vec4;
+template <> struct Vec4<float> {
+  static __device__ __forceinline__ float4 load(const float* p, int c4) { return reinterpret_cast<const float4*>(p)[c4]; }
+  static __device__ __forceinline__ void store(float* p, int c4, float4 v) { reinterpret_cast<float4*>(p)[c4] = v; }
+};
+template <> struct Vec4<bf16_t> {
+  static __device__ __forceinline__ float4 load(const bf16_t* p, int c4) {
+    const uint2 u = reinterpret_cast<const uint2*>(p)[c4];
+    return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                       __uint_as_float(u.y & 0xffff0000u));
+  }
+  static __device__ __forceinline__ void store(bf16_t* p, int c4, float4 v) {
+    uint2 u;
+    u.x = (uint32_t)f2bf(v.x) | ((uint32_t)f2bf(v.y) << 16);
+    u.y = (uint32_t)f2bf(v.z) | ((uint32_t)f2bf(v.w) << 16);
+    reinterpret_cast<uint2*>(p)[c4] = u;
+  }
+};
+
+// The forward's first launch: three kinds of 256-thread block in one grid (as a
+// launch of its own the RoPE table held the embedding back by 5 us; its float64
+// pow and sincos now run beside the embedding's stores):
+//  block 0 clears the attention tickets and writes the error word: clean, or
+//    ERR_TOKEN_RANGE if any id is outside [0, V) -- one plain store of one
+//    thread, so nothing has to be cleared beforehand;
+//  the next nrope blocks write the RoPE tables: angle = pos * base^(-2j/hd) in
+//    float64 (positions reach 8k, where a float32 angle would already be off
+//    by ~1e-3 rad), stored as float32 cos/sin;
+//  every further block gathers a row: row m = b rows + i takes token x[b, row0 +
+//    i]; an id outside [0, V) is never used as an address: the row is zero.
+// Rows move four elements per lane and access where the row allows it (VEC).
+struct EmbedArgs {
+  const int32_t* x;
+  const void* E;
+  float* h;
+  int M, rows, L, row0, d, V;
+  int* err;
+  int* zero;
+  int nzero;
+  float* cosb;
+  float* sinb;
+  int nrope, hd;
+  double base;
+};
+
+template <typename T, bool VEC>
+__global__ void __launch_bounds__(256) embed_kernel(EmbedArgs a) {
+  const int tid = threadIdx.x;
+  if (blockIdx.x == 0) {
+    for (int z = tid; z < a.nzero; z += 256) a.zero[z] = 0;
+    int bad = 0;
+#pragma unroll 8
+    for (int m = tid; m < a.M; m += 256) {
+      const int b = m / a.rows, tok = a.x[(size_t)b * a.L + a.row0 + m - b * a.rows];
+      bad |= tok < 0 || tok >= a.V;
+    }
+    bad = __syncthreads_or(bad);
+    if (tid == 0 && a.err) *a.err = bad ? (int)ERR_TOKEN_RANGE : 0;
+    return;
+  }
+  if ((int)blockIdx.x <= a.nrope) {
+    const int half = a.hd / 2, i = ((int)blockIdx.x - 1) * 256 + tid;
+    if (i >= a.L * half) return;
+    const int pos = i / half, j = i % half;
+    const double inv_freq = pow(a.base, -2.0 * (double)j / (double)a.hd);
+    double sn, cs;
+    sincos((double)pos * inv_freq, &sn, &cs);
+    a.cosb[i] = (float)cs;
+    a.sinb[i] = (float)sn;
+    return;
+  }
+  const int m = (int)blockIdx.x - 1 - a.nrope, b = m / a.rows, i = m - b * a.rows;
+  const int tok = a.x[(size_t)b * a.L + a.row0 + i];
+  const bool ok = tok >= 0 && tok < a.V;
+  const T* src = static_cast<const T*>(a.E) + (size_t)(ok ? tok : 0) * a.d;
+  float* dst = a.h + (size_t)m * a.d;
+  if (VEC) {
+    const int d4 = a.d / 4;
+#pragma unroll 4
+    for (int c = tid; c < d4; c += 256)
+      Vec4<float>::store(dst, c, ok ? Vec4<T>::load(src, c) : make_float4(0.f, 0.f, 0.f, 0.f));
+  } else {
+    for (int c = tid; c < a.d; c += 256) dst[c] = ok ? Act<T>::load(src, c) : 0.f;
+  }
 }
 
 void launch_embed(const int32_t* x, const void* E, int dtype, float* h, int B, int rows, int L, int row0, int d,
-                  int V, int* err, hipStream_t s, int* zero, int nzero) {
+                  int V, int* err, hipStream_t s, int* zero, int nzero, const RopeTable* rope) {
   const int M = B * rows;
   if (M == 0) return;
-  if (!zero) nzero = 0;
+  EmbedArgs a{x, E, h, M, rows, L, row0, d, V, err, zero, zero ? nzero : 0, nullptr, nullptr, 0, 0, 0.0};
+  if (rope) {
+    a.cosb = rope->cosb;
+    a.sinb = rope->sinb;
+    a.hd = rope->hd;
+    a.base = rope->base;
+    a.nrope = ceil_div((long)L * (rope->hd / 2), 256);
+  }
+  const bool vec = d % 4 == 0 && ((uintptr_t)E | (uintptr_t)h) % 16 == 0;
+  const dim3 grid(1 + a.nrope + M), blk(256);
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, blk, 0, s, a); };
   if (dtype == 0)
-    hipLaunchKernelGGL(embed_kernel<float>, dim3(M), dim3(256), 0, s, x, (const float*)E, h, rows, L, row0, d, V,
-                       err, zero, nzero);
+    vec ? go(embed_kernel<float, true>) : go(embed_kernel<float, false>);
   else
-    hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(M), dim3(256), 0, s, x, (const bf16_t*)E, h, rows, L, row0, d, V,
-                       err, zero, nzero);
+    vec ? go(embed_kernel<bf16_t, true>) : go(embed_kernel<bf16_t, false>);
   DLLM_LAUNCH_CHECK("embed");
-}
-
-// angle = pos * base^(-2j/hd) in float64 (positions reach 8k, where a float32
-// angle would already be off by ~1e-3 rad), stored as float32 cos/sin.  Thread
-// 0 also clears the forward's error word (err non-null).
-__global__ void rope_table_kernel(float* cosb, float* sinb, int L, int half, double base, int hd, int* err) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0 && err) *err = 0;
-  if (i >= L * half) return;
-  const int pos = i / half, j = i % half;
-  const double inv_freq = pow(base, -2.0 * (double)j / (double)hd);
-  double sn, cs;
-  sincos((double)pos * inv_freq, &sn, &cs);
-  cosb[i] = (float)cs;
-  sinb[i] = (float)sn;
-}
-
-void launch_rope_table(float* cosb, float* sinb, int L, int hd, double base, int* err, hipStream_t s) {
-  const int n = L * (hd / 2);
-  if (n == 0) return;
-  hipLaunchKernelGGL(rope_table_kernel, dim3(ceil_div(n, 256)), dim3(256), 0, s, cosb, sinb, L, hd / 2, base, hd,
-                     err);
-  DLLM_LAUNCH_CHECK("rope_table");
 }
 
 // RMSNorm of one row per 256-thread block.  The sum of squares is accumulated
@@ -101,25 +155,6 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(const float* __restrict__ 
 // row is read once, as float4, into registers (NV per thread) and written from
 // there.  The float64 sum of squares runs over a different fixed order; its
 // float32 result is the same in all but astronomically rare ties.
-template <typename T> struct Vec4;
-template <> struct Vec4<float> {
-  static __device__ __forceinline__ float4 load(const float* p, int c4) { return reinterpret_cast<const float4*>(p)[c4]; }
-  static __device__ __forceinline__ void store(float* p, int c4, float4 v) { reinterpret_cast<float4*>(p)[c4] = v; }
-};
-template <> struct Vec4<bf16_t> {
-  static __device__ __forceinline__ float4 load(const bf16_t* p, int c4) {
-    const uint2 u = reinterpret_cast<const uint2*>(p)[c4];
-    return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
-                       __uint_as_float(u.y & 0xffff0000u));
-  }
-  static __device__ __forceinline__ void store(bf16_t* p, int c4, float4 v) {
-    uint2 u;
-    u.x = (uint32_t)f2bf(v.x) | ((uint32_t)f2bf(v.y) << 16);
-    u.y = (uint32_t)f2bf(v.z) | ((uint32_t)f2bf(v.w) << 16);
-    reinterpret_cast<uint2*>(p)[c4] = u;
-  }
-};
-
 template <typename TG, typename TO, int NV>
 __global__ void __launch_bounds__(256) rmsnorm_vec_kernel(const float* __restrict__ h, const TG* __restrict__ g,
                                                           TO* __restrict__ out, int rows, int L, int row0, int d,

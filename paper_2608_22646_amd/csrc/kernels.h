@@ -9,13 +9,18 @@ namespace dllm {
 // cannot represent and reported (then cleared) by the commit kernel.
 enum { ERR_TOKEN_RANGE = 1, ERR_V_RANGE = 2 };
 // h[b*rows + i, :] = float(E[x[b*L + row0 + i], :]) for b < B, i < rows.  An id
-// outside [0, V) gathers a zero row and sets ERR_TOKEN_RANGE in *err.  The
-// nzero ints at zero (the forward's attention tickets) are set to 0.
+// outside [0, V) gathers a zero row; *err is set to ERR_TOKEN_RANGE if there is
+// one and to 0 otherwise.  The nzero ints at zero (the forward's attention
+// tickets) are set to 0.  With rope the same launch writes cos/sin [L, hd/2] of
+// pos * base^(-2j/hd), evaluated in float64, stored float32.
+struct RopeTable {
+  float* cosb;
+  float* sinb;
+  int hd;
+  double base;
+};
 void launch_embed(const int32_t* x, const void* E, int dtype, float* h, int B, int rows, int L, int row0, int d,
-                  int V, int* err, hipStream_t s, int* zero = nullptr, int nzero = 0);
-// cos/sin [L, hd/2] of pos * base^(-2j/hd), evaluated in float64, stored float32;
-// a non-null err word is cleared first (a forward starts with a clean word).
-void launch_rope_table(float* cosb, float* sinb, int L, int hd, double base, int* err, hipStream_t s);
+                  int V, int* err, hipStream_t s, int* zero = nullptr, int nzero = 0, const RopeTable* rope = nullptr);
 // out[b*rows + i, :] = act(RMSNorm(h[b*L + row0 + i, :]) * g) for b < B, i < rows.
 void launch_rmsnorm(const float* h, const void* g, void* out, int dtype, int B, int rows, int L, int row0,
                     int d, float eps, hipStream_t s);
