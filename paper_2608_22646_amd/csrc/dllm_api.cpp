@@ -77,6 +77,7 @@ struct Layout {
   size_t part_m, part_s, part_i, ticket, hbf;    // bf16 head
   size_t splitk;                                 // bf16 split-K GEMM partials
   size_t attn_part, attn_ticket;                 // bf16 key-split attention states and tickets
+  size_t af, of, uf;                             // bf16, few rows: normed rows, attention output, u in operand order
   size_t conf, argmax, all_done, err;            // step scratch
   size_t total;
 };
@@ -114,6 +115,10 @@ Layout make_layout(const dllm_model_cfg& c, int B, int L, int rows) {
     o.hbf = take((size_t)HEAD_FRAG_ROWS * d * 2);
     o.attn_ticket = take((size_t)B * c.n_heads * 4);
     o.attn_part = take(attn_split_bytes(B, c.n_heads));
+    const size_t fr = std::min<size_t>((M + 31) / 32 * 32, GEMM_ROWS_MAX);
+    o.af = take(fr * d * 2);
+    o.of = take(fr * c.n_heads * hd * 2);
+    o.uf = take(fr * F * 2);
   }
   // sized by the head rows
   o.hb = take(R * d * act);
@@ -247,15 +252,15 @@ void gemm_bf16(const dllm_model* m, GemmArgs g, void* ws, const Layout& lay, hip
 
 // RMSNorm of every row of h into out; split-K partials still pending from the
 // previous residual GEMM (pend non-null with split > 0) are added to h first,
-// in the same pass, and then cleared.
-void norm_rows_bf16(const dllm_model* m, float* h, PendingResid* pend, const void* gain, void* out, int B, int L,
-                    hipStream_t s) {
+// in the same pass, and then cleared.  outf (few rows): operand-order copy.
+void norm_rows_bf16(const dllm_model* m, float* h, PendingResid* pend, const void* gain, void* out, bf16_t* outf, int B,
+                    int L, hipStream_t s) {
   const auto& c = m->cfg;
   ProfScope p(m, PK_NORM, s);
-  if (pend && pend->split > 0) {
-    launch_resid_rmsnorm(h, *pend, static_cast<const bf16_t*>(gain), static_cast<bf16_t*>(out), B * L, c.d_model,
-                         c.rms_eps, s);
-    *pend = PendingResid{};
+  if (outf || (pend && pend->split > 0)) {
+    launch_resid_rmsnorm(h, pend ? *pend : PendingResid{}, static_cast<const bf16_t*>(gain), static_cast<bf16_t*>(out),
+                         outf, B * L, c.d_model, c.rms_eps, s);
+    if (pend) *pend = PendingResid{};
   } else {
     launch_rmsnorm(h, gain, out, 1, B, L, L, 0, c.d_model, c.rms_eps, s);
   }
@@ -322,11 +327,16 @@ void run_layer_bf16(const dllm_model* m, int layer, int part, int B, int L, void
   const int M = B * Lq, d = c.d_model, hd = c.head_dim;
   float* h = at<float>(ws, lay.h);
   PendingResid mid;  // output-projection partials, consumed by the MLP norm
+  const bool few = m->packed && gemm_rows_path(M);  // operand-order copies for the few-row GEMMs
+  bf16_t* af = few ? at<bf16_t>(ws, lay.af) : nullptr;
+  bf16_t* of = few ? at<bf16_t>(ws, lay.of) : nullptr;
+  bf16_t* uf = few ? at<bf16_t>(ws, lay.uf) : nullptr;
   if (part == 0 || part == 2) {
-    norm_rows_bf16(m, h, carry_in, W(m, base + 0), at<void>(ws, lay.a_attn), B, Lq, s);
+    norm_rows_bf16(m, h, carry_in, W(m, base + 0), at<void>(ws, lay.a_attn), af, B, Lq, s);
     GemmArgs g = layer_gemm(m, layer, 0);
     g.M = M;
     g.A = at<bf16_t>(ws, lay.a_attn);
+    g.Af = af;
     g.q = at<bf16_t>(ws, lay.q);
     g.k = rows && rows->k ? static_cast<bf16_t*>(rows->k) : at<bf16_t>(ws, lay.k);
     g.vt = rows && rows->vt ? static_cast<f16_t*>(rows->vt) : at<f16_t>(ws, lay.vt);
@@ -342,25 +352,29 @@ void run_layer_bf16(const dllm_model* m, int layer, int part, int B, int L, void
     gemm_bf16(m, g, ws, lay, s, PK_QKV);
     {
       ProfScope p(m, PK_ATTN, s);
-      launch_attn_bf16(g.q, g.k, g.vt, at<bf16_t>(ws, lay.attn), B, Lq, L, c.n_heads, c.n_kv_heads, s,
+      launch_attn_bf16(g.q, g.k, g.vt, at<bf16_t>(ws, lay.attn), of, B, Lq, L, c.n_heads, c.n_kv_heads, s,
                        at<float>(ws, lay.attn_part), at<int>(ws, lay.attn_ticket));
     }
     GemmArgs o = layer_gemm(m, layer, 1);
     o.M = M;
     o.A = at<bf16_t>(ws, lay.attn);
+    o.Af = of;
     o.resid = h;
     gemm_bf16(m, o, ws, lay, s, PK_OPROJ, part == 2 ? &mid : nullptr);
   }
   if (part == 1 || part == 2) {
-    norm_rows_bf16(m, h, part == 1 ? carry_in : &mid, W(m, base + 5), at<void>(ws, lay.a_mlp), B, Lq, s);
+    norm_rows_bf16(m, h, part == 1 ? carry_in : &mid, W(m, base + 5), at<void>(ws, lay.a_mlp), af, B, Lq, s);
     GemmArgs g = layer_gemm(m, layer, 2);
     g.M = M;
     g.A = at<bf16_t>(ws, lay.a_mlp);
+    g.Af = af;
     g.out = at<bf16_t>(ws, lay.u);
+    g.outf = uf;
     gemm_bf16(m, g, ws, lay, s, PK_GATEUP);
     GemmArgs dn = layer_gemm(m, layer, 3);
     dn.M = M;
     dn.A = at<bf16_t>(ws, lay.u);
+    dn.Af = uf;
     dn.resid = h;
     gemm_bf16(m, dn, ws, lay, s, PK_DOWN, carry_out);
   }

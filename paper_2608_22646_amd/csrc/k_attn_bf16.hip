@@ -46,6 +46,23 @@ __device__ __forceinline__ int3 attn_block(int nqb, int Hq) {
   const int qb = lin % nqb, r = lin / nqb;
   return make_int3(qb, r % Hq, r / Hq);
 }
+// Output dimensions d .. d + 3 (or .. d + 7) of head h for token row m = b Lq +
+// query: row-major, and with outf (few rows in all: the output projection then
+// streams its row operands) also in MFMA operand order.
+struct AttnOut {
+  bf16_t* out;
+  bf16_t* outf;
+  int MB, Hq;
+  __device__ __forceinline__ void store4(size_t m, int h, int d, uint2 w) const {
+    *reinterpret_cast<uint2*>(out + m * ((size_t)Hq * HD) + (size_t)h * HD + d) = w;
+    if (outf) *reinterpret_cast<uint2*>(outf + frag_at(MB, (int)m, h * HD + d)) = w;
+  }
+  __device__ __forceinline__ void store8(size_t m, int h, int d, uint4 w) const {
+    *reinterpret_cast<uint4*>(out + m * ((size_t)Hq * HD) + (size_t)h * HD + d) = w;
+    if (outf) *reinterpret_cast<uint4*>(outf + frag_at(MB, (int)m, h * HD + d)) = w;
+  }
+};
+
 constexpr int K_BYTES = KT * HD * 2, V_BYTES = HD * KT * 2, STAGE = K_BYTES + V_BYTES;
 
 // XOR swizzles sized for the 64 banks (256 bytes) that one 16-lane pass of
@@ -79,8 +96,8 @@ __device__ __forceinline__ float sum_pair32(float x) {
 }
 
 __global__ void __launch_bounds__(256, 1) attn_bf16_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
-                                                           const f16_t* __restrict__ vt, bf16_t* __restrict__ out,
-                                                           int Lq, int L, int Hq, int Hkv) {
+                                                           const f16_t* __restrict__ vt, AttnOut out, int Lq, int L,
+                                                           int Hq, int Hkv) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int3 wb = attn_block((Lq + QW * NW - 1) / (QW * NW), Hq);
@@ -225,7 +242,6 @@ __global__ void __launch_bounds__(256, 1) attn_bf16_kernel(const bf16_t* __restr
   const float inv = 1.0f / l_tot;
   const int qi = q0 + lq;
   if (qi >= Lq) return;
-  bf16_t* orow = out + ((size_t)b * Lq + qi) * ((size_t)Hq * HD) + (size_t)h * HD;
 #pragma unroll
   for (int ds = 0; ds < 4; ++ds)
 #pragma unroll
@@ -234,7 +250,7 @@ __global__ void __launch_bounds__(256, 1) attn_bf16_kernel(const bf16_t* __restr
       uint2 w;
       w.x = pack_bf16x2(o[ds][rg * 4 + 0] * inv, o[ds][rg * 4 + 1] * inv);
       w.y = pack_bf16x2(o[ds][rg * 4 + 2] * inv, o[ds][rg * 4 + 3] * inv);
-      *reinterpret_cast<uint2*>(orow + d) = w;
+      out.store4((size_t)b * Lq + qi, h, d, w);
     }
 }
 
@@ -268,7 +284,7 @@ template <int NW>
 __global__ void __launch_bounds__(64 * NW, 1) attn_stream_kernel(const bf16_t* __restrict__ q,
                                                                  const bf16_t* __restrict__ k,
                                                                  const f16_t* __restrict__ vt,
-                                                                 bf16_t* __restrict__ out, int Lq, int L, int Hq, int Hkv) {
+                                                                 AttnOut out, int Lq, int L, int Hq, int Hkv) {
 #if defined(__HIP_DEVICE_COMPILE__)
   // D tiles in flight ahead of the one in use
   constexpr int D = 2, S = D + 1, PER_STAGE = 32 / NW;  // 16 K + 16 V^T DMA instructions per tile
@@ -444,7 +460,6 @@ __global__ void __launch_bounds__(64 * NW, 1) attn_stream_kernel(const bf16_t* _
   const float inv = 1.0f / l_tot;
   const int qi = q0 + lq;
   if (qi >= Lq) return;
-  bf16_t* orow = out + ((size_t)b * Lq + qi) * ((size_t)Hq * HD) + (size_t)h * HD;
 #pragma unroll
   for (int ds = 0; ds < 4; ++ds)
 #pragma unroll
@@ -453,7 +468,7 @@ __global__ void __launch_bounds__(64 * NW, 1) attn_stream_kernel(const bf16_t* _
       uint2 w;
       w.x = pack_bf16x2(o[ds][rg * 4 + 0] * inv, o[ds][rg * 4 + 1] * inv);
       w.y = pack_bf16x2(o[ds][rg * 4 + 2] * inv, o[ds][rg * 4 + 3] * inv);
-      *reinterpret_cast<uint2*>(orow + d) = w;
+      out.store4((size_t)b * Lq + qi, h, d, w);
     }
 #endif
 }
@@ -477,7 +492,7 @@ template <int QG>
 __global__ void __launch_bounds__(64 * QG * KGRP, 1) attn_kv4_kernel(const bf16_t* __restrict__ q,
                                                                     const bf16_t* __restrict__ k,
                                                                     const f16_t* __restrict__ vt,
-                                                                    bf16_t* __restrict__ out, int Lq, int L, int Hq, int Hkv) {
+                                                                    AttnOut out, int Lq, int L, int Hq, int Hkv) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int NW = QG * KGRP, S = 2;
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -698,8 +713,7 @@ __global__ void __launch_bounds__(64 * QG * KGRP, 1) attn_kv4_kernel(const bf16_
     for (int it = tid; it < QG * QW * 16; it += NW * 64) {
       const int row = it >> 4, ch = it & 15, qi = qb0 + row;
       if (qi < Lq)
-        *reinterpret_cast<uint4*>(out + ((size_t)b * Lq + qi) * ((size_t)Hq * HD) + (size_t)h * HD + ch * 8) =
-            *reinterpret_cast<const uint4*>(stg + row * OPK + ch * 16);
+        out.store8((size_t)b * Lq + qi, h, ch * 8, *reinterpret_cast<const uint4*>(stg + row * OPK + ch * 16));
     }
     return;
   }
@@ -775,8 +789,7 @@ __global__ void __launch_bounds__(64 * QG * KGRP, 1) attn_kv4_kernel(const bf16_
   for (int it = 0; it < 8; ++it) {
     const int row = it * 4 + (lane >> 4), ch = lane & 15, qi = q0 + row;
     if (qi < Lq)
-      *reinterpret_cast<uint4*>(out + ((size_t)b * Lq + qi) * ((size_t)Hq * HD) + (size_t)h * HD + ch * 8) =
-          *reinterpret_cast<const uint4*>(stg + row * OP + ch * 16);
+      out.store8((size_t)b * Lq + qi, h, ch * 8, *reinterpret_cast<const uint4*>(stg + row * OP + ch * 16));
   }
 #endif
 }
@@ -801,7 +814,7 @@ template <int NWS>
 __global__ void __launch_bounds__(64 * NWS, 1) attn_split_kernel(const bf16_t* __restrict__ q,
                                                                  const bf16_t* __restrict__ k,
                                                                  const f16_t* __restrict__ vt,
-                                                                 bf16_t* __restrict__ out, float* __restrict__ part,
+                                                                 AttnOut out, float* __restrict__ part,
                                                                  int* __restrict__ ticket, int Lq, int L, int Hq,
                                                                  int Hkv, int NS) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -969,7 +982,6 @@ __global__ void __launch_bounds__(64 * NWS, 1) attn_split_kernel(const bf16_t* _
   auto store_rows = [&](const f32x16_t* oo, int ds0, int nds, float l) {
     const float inv = 1.0f / sum_pair32(l);
     if (lq >= Lq) return;
-    bf16_t* orow = out + ((size_t)b * Lq + lq) * ((size_t)Hq * HD) + (size_t)h * HD;
     for (int ds = ds0; ds < ds0 + nds; ++ds)
 #pragma unroll
       for (int rg = 0; rg < 4; ++rg) {
@@ -977,7 +989,7 @@ __global__ void __launch_bounds__(64 * NWS, 1) attn_split_kernel(const bf16_t* _
         uint2 w;
         w.x = pack_bf16x2(oo[ds - ds0][rg * 4 + 0] * inv, oo[ds - ds0][rg * 4 + 1] * inv);
         w.y = pack_bf16x2(oo[ds - ds0][rg * 4 + 2] * inv, oo[ds - ds0][rg * 4 + 3] * inv);
-        *reinterpret_cast<uint2*>(orow + d) = w;
+        out.store4((size_t)b * Lq + lq, h, d, w);
       }
   };
   if (NS == 1) {
@@ -1053,9 +1065,11 @@ __global__ void __launch_bounds__(64 * NWS, 1) attn_split_kernel(const bf16_t* _
 
 size_t attn_split_bytes(int B, int Hq) { return (size_t)std::max(B * Hq, 512) * SPLIT_STATE; }
 
-void launch_attn_bf16(const bf16_t* q, const bf16_t* k, const f16_t* vt, bf16_t* out, int B, int Lq, int L, int Hq,
-                      int Hkv, hipStream_t s, float* split_part, int* split_ticket) {
+void launch_attn_bf16(const bf16_t* q, const bf16_t* k, const f16_t* vt, bf16_t* out_rows, bf16_t* outf, int B, int Lq,
+                      int L, int Hq, int Hkv, hipStream_t s, float* split_part, int* split_ticket) {
   if (B * Lq == 0) return;
+  if (outf && B * Lq > GEMM_ROWS_MAX) throw HipError("attn: the operand-order output holds 64 rows");
+  const AttnOut out{out_rows, outf, ceil_div(B * Lq, 32), Hq};
   if (Lq <= QW && split_part && split_ticket) {
     // one query group per head: the keys split over NS workgroups of 4 waves
     // when that fills 7/8 of the CUs, else of 2 waves (shorter sequences)

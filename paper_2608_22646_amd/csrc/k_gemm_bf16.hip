@@ -798,61 +798,74 @@ __global__ void pack_gemm_weights_kernel(GemmArgs g, bf16_t* __restrict__ out, s
   }
 }
 
-// GEMM of at most 64 rows from the packed copy, register-direct (the LM head's
-// streaming design): wave w of the grid owns GW 32-row groups of Bv (group
-// block w % ngb) and the k-slices [z KS / S, (z + 1) KS / S) of split z =
-// w / ngb; per 16-k slice it loads its GW 1 KiB W operands (contiguous runs of
-// the copy, non-temporal) and MB X operands (rows 32 mb + l % 32 of A, zero
-// past M) into a P-deep register ring -- no LDS, no barrier -- and runs GW x MB
-// MFMAs with W as the A operand (a lane ends with 16 columns n of one row m).
-// It writes float32 partials part[z, m, n]; the split-K epilogues finish them.
-// Loads complete in issue order, so before slice u only the (GW + MB) (P - 1)
-// loads of the slices after it may be outstanding.
-struct RowsArgs {
-  const bf16_t* A;   // [M, K]
-  const bf16_t* Wp;  // packed Bv
-  float* part;       // [S, M, N]
-  int M, N, K, S, ngb;
+// GEMM of at most 64 rows from the packed copy (a cached step's block rows),
+// bound by streaming the weights from HBM once.  A workgroup of NW waves owns GW
+// 32-row groups of Bv and the 16-k slices of K split z; its waves take the
+// slices round robin, each streaming GW 1 KiB W operands (non-temporal) and MB
+// 1 KiB row operands per slice straight into a P-deep register ring -- no LDS,
+// no barrier in the loop -- and running GW x MB MFMAs with W as the A operand.
+// The row operands come from an operand-order copy of A that its producer
+// wrote next to the row-major one (slice u, 32-row block mb: 1 KiB at (u MB +
+// mb) in lane order), so every load is one contiguous run.  The NW partial sums
+// meet in LDS in wave order and the workgroup finishes the GEMM's epilogue.
+//
+// Why this split: the bytes in flight per CU bound a short stream (100 MB,
+// no arithmetic: 192 workgroups of 4 waves x 2 groups 32.8 us, of 8 waves 20.8,
+// of 16 waves 17.6; 256 workgroups of 4 waves splitting K over the grid 21.3), and
+// splitting K inside the workgroup leaves no partial sums to write, read back and
+// finish in a launch of their own.  One wave per (group block, K split) over the
+// grid with partials for every projection (the kernel this replaces) took, for
+// LLaDA-8B widths at 32 rows: q/k/v 22.1 + 5.0 us with its epilogue, o 11.8,
+// gate/up 36.8 + 4.8, down 22.1; this one 22.3, 9.5, 32.4 and 20.1 (4.5, 3.5, 6.2
+// and 5.0 TB/s; q/k/v has 192 workgroups of two groups for 256 CUs).
+template <int GW, int MB>
+struct RowsTile {
+  // sixteen waves where the accumulators leave each of them a ring (128
+  // registers at four waves per SIMD), else eight
+  static constexpr int NW = GW * MB <= 2 ? 16 : 8;
+  static constexpr int BUDGET = (NW == 16 ? 104 : 226) - 16 * GW * MB;
+  static constexpr int PR = BUDGET / (4 * (GW + MB));
+  static constexpr int P = PR > 8 ? 8 : PR;
+  static constexpr int NB = GW * MB;         // 32 x 32 output blocks
+  static constexpr int RM = 32 / NW, RB = NB < RM ? NB : RM;  // ... merged per round (128 KiB of LDS)
+  static constexpr size_t RED = (size_t)NW * RB * 4096, LDS = RED + (size_t)NB * 4096;
+  static_assert(P >= 2 && LDS <= 160 * 1024, "ring and merge area fit");
 };
 
-template <int GW, int MB, int P>
-__global__ void __launch_bounds__(256, 2) gemm_rows_kernel(RowsArgs a) {
+template <int EPI, int GW, int MB>
+__global__ void __launch_bounds__((64 * RowsTile<GW, MB>::NW), 1) gemm_rows_kernel(GemmArgs g, int S) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  static_assert((GW + MB) * (P - 1) < 64, "vmcnt range");
-  const int lane = threadIdx.x & 63;
-  const int wg = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (wg >= a.ngb * a.S) return;
-  const int gb = wg % a.ngb, z = wg / a.ngb;
-  const int KS = a.K / 16, nk = a.K / 64;
-  const int u0 = (int)((long)z * KS / a.S), n = (int)((long)(z + 1) * KS / a.S) - u0;
-  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)a.Wp, 0, 0x7fffffff, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)a.A, 0, 0x7fffffff, 0x00020000);
-  const int lr = lane & 31, half = lane >> 5;
-  // group G = gb GW + j lies in 256-row tile G / 8 at position G % 8
+  using RT = RowsTile<GW, MB>;
+  constexpr int NW = RT::NW, P = RT::P, NB = RT::NB, NTH = 64 * NW;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ng = g.N / 32, ngb = (ng + GW - 1) / GW, gb = blockIdx.x % ngb, z = blockIdx.x / ngb;
+  const int KS = g.K / 16, nk = g.K / 64;
+  const int u0 = (int)((long)z * KS / S) + wave, u1 = (int)((long)(z + 1) * KS / S);
+  const int n = u1 > u0 ? (u1 - u0 + NW - 1) / NW : 0;  // this wave's slices u0, u0 + NW, ..
+  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)g.Wp, 0, 0x7fffffff, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)g.Af, 0, 0x7fffffff, 0x00020000);
+  // group G lies in 256-row tile G / 8 at position G % 8 (past the last group:
+  // the last again, never stored)
   uint32_t wbase[GW];
 #pragma unroll
   for (int j = 0; j < GW; ++j) {
-    const int G = gb * GW + j;
-    wbase[j] = (uint32_t)(((size_t)(G >> 3) * nk * 8 + (G & 7)) * 4 * 1024 + lane * 16);
-  }
-  uint32_t xoff[MB];
-  bool xok[MB];
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const int m = 32 * mb + lr;
-    xok[mb] = m < a.M;
-    xoff[mb] = (uint32_t)(((size_t)min(m, a.M - 1) * a.K + half * 8) * 2);
+    const int G = min(gb * GW + j, ng - 1);
+    wbase[j] = (uint32_t)(((size_t)(G >> 3) * nk * 8 + (G & 7)) * 4096) + lane * 16;
   }
   typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
   u32x4_t wbuf[P][GW], xbuf[P][MB];
-  auto load = [&](int u, int slot) {
-    const int us = u0 + u, kb = us >> 2, sl = us & 3;
+  // slice i of this wave; past its last one the buffer bound returns zeros, so
+  // the ring needs no branches (which would make every wait a wait for all)
+  auto load = [&](int i, int slot) {
+    const int us = u0 + NW * i;
+    const uint32_t past = i < n ? 0u : 0x80000000u;
 #pragma unroll
     for (int j = 0; j < GW; ++j)
-      wbuf[slot][j] = __builtin_amdgcn_raw_buffer_load_b128(rw, wbase[j] + (uint32_t)(kb * 32768 + sl * 1024), 0, 2);
+      wbuf[slot][j] = __builtin_amdgcn_raw_buffer_load_b128(rw, wbase[j] | past, (us >> 2) * 32768 + (us & 3) * 1024, 2);
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
-      xbuf[slot][mb] = __builtin_amdgcn_raw_buffer_load_b128(rx, xoff[mb] + (uint32_t)(us * 32), 0, 0);
+      xbuf[slot][mb] = __builtin_amdgcn_raw_buffer_load_b128(rx, lane * 16 | past, (us * MB + mb) * 1024, 0);
   };
   f32x16_t acc[GW][MB];
 #pragma unroll
@@ -861,76 +874,169 @@ __global__ void __launch_bounds__(256, 2) gemm_rows_kernel(RowsArgs a) {
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[j][mb][r] = 0.f;
-#pragma unroll
-  for (int p = 0; p < P; ++p)
-    if (p < n) load(p, p);
-  for (int b0 = 0; b0 < n; b0 += P) {
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      const int u = b0 + p;
-      if (u < n) {
-        if (u + P - 1 < n)
-          __builtin_amdgcn_s_waitcnt((((GW + MB) * (P - 1)) & 15) | (7 << 4) | (15 << 8) |
-                                     ((((GW + MB) * (P - 1)) >> 4) << 14));
-        else
-          __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));  // the last slices: fewer later loads issued
-        bf16x8_t xf[MB];
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          xf[mb] = __builtin_bit_cast(bf16x8_t, xbuf[p][mb]);
-          if (!xok[mb]) xf[mb] = bf16x8_t{0, 0, 0, 0, 0, 0, 0, 0};
-        }
-#pragma unroll
-        for (int j = 0; j < GW; ++j)
-#pragma unroll
-          for (int mb = 0; mb < MB; ++mb)
-            acc[j][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, wbuf[p][j]), xf[mb],
-                                                                acc[j][mb], 0, 0, 0);
-        if (u + P < n) load(u + P, p);
-      }
-    }
-  }
-  // partials: lane holds columns n = 32 G + 8 (r / 4) + 4 half + r % 4 of row m = 32 mb + l % 32
-  float* part = a.part + (size_t)z * a.M * a.N;
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const int m = 32 * mb + lr;
-    if (m >= a.M) continue;
+  auto mma = [&](int slot) {
 #pragma unroll
     for (int j = 0; j < GW; ++j)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int nn = (gb * GW + j) * 32 + 8 * q + 4 * half;
-        *reinterpret_cast<float4*>(part + (size_t)m * a.N + nn) =
-            make_float4(acc[j][mb][4 * q], acc[j][mb][4 * q + 1], acc[j][mb][4 * q + 2], acc[j][mb][4 * q + 3]);
+      for (int mb = 0; mb < MB; ++mb)
+        acc[j][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, wbuf[slot][j]),
+                                                            __builtin_bit_cast(bf16x8_t, xbuf[slot][mb]), acc[j][mb],
+                                                            0, 0, 0);
+  };
+#pragma unroll
+  for (int p = 0; p < P; ++p) load(p, p);
+  for (int i0 = P; i0 < n; i0 += P) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      mma(p);
+      load(i0 + p, p);
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < P; ++p) mma(p);
+
+  // the RoPE values this thread's eight q or k pairs need, loaded under the merge
+  const int G0 = gb * GW, gn = min(GW, ng - G0);
+  float cs[8], sn[8];
+  const int ec = tid % (2 * gn), em = tid / (2 * gn);  // (group and half, token row) of the fused epilogues
+  if constexpr (EPI == EPI_QKV_ROPE) {
+    const int nq = g.Hq * 128, n0 = 32 * (G0 + (ec >> 1));
+    if (em < g.M && n0 < nq + g.Hkv * 128) {
+      const int d = 16 * ((n0 % 128) >> 5) + 8 * (ec & 1);  // nq is a whole number of heads
+      const size_t o = (size_t)(g.pos0 + em % g.Lq) * 64 + d;
+#pragma unroll
+      for (int e = 0; e < 8; e += 4) {
+        *reinterpret_cast<float4*>(cs + e) = *reinterpret_cast<const float4*>(g.cosb + o + e);
+        *reinterpret_cast<float4*>(sn + e) = *reinterpret_cast<const float4*>(g.sinb + o + e);
       }
+    }
+  }
+
+  // sum over the waves in wave order: red [wave][block of the round][16][64],
+  // fin [block][16][64] (register r, lane l of an MFMA result: Bv row 8 (r / 4)
+  // + 4 (l / 32) + r % 4 of group j, token row l % 32 of block mb)
+  float* red = reinterpret_cast<float*>(lds);
+  float* fin = reinterpret_cast<float*>(lds + RT::RED);
+  constexpr int RB = RT::RB;
+#pragma unroll
+  for (int c0 = 0; c0 < NB; c0 += RB) {
+    if (c0 > 0) __syncthreads();
+#pragma unroll
+    for (int c = 0; c < RB; ++c)
+      if (c0 + c < NB) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) red[((wave * RB + c) * 16 + r) * 64 + lane] = acc[(c0 + c) / MB][(c0 + c) % MB][r];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < RB; ++c)
+      if (c0 + c < NB) {
+#pragma unroll
+        for (int r = wave; r < 16; r += NW) {
+          float v = red[(c * 16 + r) * 64 + lane];
+#pragma unroll
+          for (int w = 1; w < NW; ++w) v += red[((w * RB + c) * 16 + r) * 64 + lane];
+          fin[((c0 + c) * 16 + r) * 64 + lane] = v;
+        }
+      }
+  }
+  __syncthreads();
+  // Bv row nl (0 .. 31) of group j, token row m
+  auto at = [&](int j, int nl, int m) {
+    return fin[((j * MB + (m >> 5)) * 16 + 4 * (nl >> 3) + (nl & 3)) * 64 + 32 * ((nl >> 2) & 1) + (m & 31)];
+  };
+  static_assert(32 * MB * 2 * GW <= NTH, "one fused-epilogue item per thread");
+  if constexpr (EPI == EPI_SWIGLU) {
+    // eight columns of u per thread: gate rows 8 q .. of the group, up rows 16 later
+    const int F = g.N / 2;
+    if (em < g.M) {
+      const int m = em, j = ec >> 1, q = ec & 1, f = 16 * (G0 + j) + 8 * q;
+      float o[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float gt = at(j, 8 * q + e, m), up = at(j, 16 + 8 * q + e, m);
+        o[e] = __fdividef(gt, 1.0f + __expf(-gt)) * up;
+      }
+      const uint4 w = make_uint4(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]), pack_bf16x2(o[4], o[5]),
+                                 pack_bf16x2(o[6], o[7]));
+      *reinterpret_cast<uint4*>(g.out + (size_t)m * F + f) = w;
+      *reinterpret_cast<uint4*>(g.outf + frag_at(MB, m, f)) = w;
+    }
+  } else if constexpr (EPI == EPI_QKV_ROPE) {
+    constexpr int HD = 128, HALF = 64;
+    const int nq = g.Hq * HD, nkv = g.Hkv * HD;
+    bool over = false;
+    if (em < g.M && 32 * (G0 + (ec >> 1)) < nq + nkv) {  // q, k: eight rotate-half pairs per thread
+      const int m = em, j = ec >> 1, q = ec & 1, n0 = 32 * (G0 + j);
+      const bool isq = n0 < nq;
+      const int rel = isq ? n0 : n0 - nq, head = rel / HD, d = 16 * ((rel % HD) >> 5) + 8 * q;
+      const int b = m / g.Lq, i = m - b * g.Lq, pos = g.pos0 + i;
+      bf16_t* dst = isq ? g.q + (((size_t)b * g.Hq + head) * g.Lq + i) * HD
+                        : g.k + (((size_t)b * g.Hkv + head) * g.L + pos) * HD;
+      float lo[8], hi[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float x1 = at(j, 8 * q + e, m), x2 = at(j, 16 + 8 * q + e, m);
+        lo[e] = x1 * cs[e] - x2 * sn[e];
+        hi[e] = x2 * cs[e] + x1 * sn[e];
+      }
+      *reinterpret_cast<uint4*>(dst + d) = make_uint4(pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]),
+                                                      pack_bf16x2(lo[4], lo[5]), pack_bf16x2(lo[6], lo[7]));
+      *reinterpret_cast<uint4*>(dst + HALF + d) = make_uint4(pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3]),
+                                                             pack_bf16x2(hi[4], hi[5]), pack_bf16x2(hi[6], hi[7]));
+    }
+    for (int it = tid; it < g.M * 32 * gn; it += NTH) {  // v: one value per thread, positions along the lanes
+      const int m = it % g.M, cc = it / g.M, j = cc >> 5, n0 = 32 * (G0 + j);
+      if (n0 < nq + nkv) continue;
+      const int rel = n0 - nq - nkv + (cc & 31), b = m / g.Lq, pos = g.pos0 + m - b * g.Lq;
+      g.vt[((size_t)b * g.Hkv * HD + rel) * g.L + pos] = v_half(at(j, cc & 31, m), over);
+    }
+    if (over && g.err) atomicOr(g.err, (int)ERR_V_RANGE);
+  } else {
+    float* part = S > 1 ? g.splitk_buf + (size_t)z * g.M * g.N : nullptr;  // partials: summed in z order later
+    for (int it = tid; it < g.M * 8 * gn; it += NTH) {
+      const int c = it % (8 * gn), m = it / (8 * gn), j = c >> 3, nl = 4 * (c & 7);
+      float4 v = make_float4(at(j, nl, m), at(j, nl + 1, m), at(j, nl + 2, m), at(j, nl + 3, m));
+      const size_t o = (size_t)m * g.N + 32 * (G0 + j) + nl;
+      if (part) {
+        *reinterpret_cast<float4*>(part + o) = v;
+      } else {
+        float4* hp = reinterpret_cast<float4*>(g.resid + o);
+        const float4 h = *hp;
+        *hp = make_float4(h.x + v.x, h.y + v.y, h.z + v.z, h.w + v.w);
+      }
+    }
   }
 #endif
 }
 
-// Groups per wave and K split of a register-direct launch, by a time model
-// measured at 32 rows on the LLaDA-8B shapes: the bytes a compute unit pulls
-// bound it (~28 GB/s per CU, 7 per wave), so a launch takes the slices of its
-// longest wave x (GW W loads + MB / 4 for the X loads, one costing a quarter
-// of a W load) x 0.146 us per KiB, times the workgroups per CU; plus the
-// float32 partials written and read back (~8 TB/s).  Fewer splits, then more
-// groups per wave, on ties.  Gate/up at 32 rows: 4 groups, split 5 (240
-// workgroups: 36 us); with split 6 a second workgroup on 32 of the CUs took 52.
+// Groups per workgroup and K split of a gemm_rows launch (only residual
+// projections split: their partials are summed by the next norm).  Time model:
+// 3 us per round of workgroups (one fits a CU), then the slower of the whole
+// matrix at 6.9 TB/s and the busiest CU's share at the rate its bytes in flight
+// allow (streams of 33-200 MB: 36 GB/s with sixteen waves or three groups and
+// more, 29 with eight waves x two groups; the row operands count a third of a W
+// operand), plus a quarter of the faster one, which shows through, and the
+// partials.  Measured at 32 rows, groups x split: 4096 x 4096 9.5 us at 1 x 2
+// (10.2 at 2 x 4, 14.1 at 1 x 1); K = 12288 20.1 at 2 x 4 (21.4 at 1 x 2, 29.6
+// at 3 x 6); gate/up of 24576 rows 32.4 at 3 (35.2 at 4, 41.1 at 2, in two rounds).
 struct RowsPlan {
   int gw, split;
 };
-RowsPlan rows_plan(int M, int N, int K) {
+RowsPlan rows_plan(int M, int N, int K, int epi) {
   const int ng = N / 32, ks = K / 16, mb = M > 32 ? 2 : 1;
   const long cus = device_cu_count();
   RowsPlan best{1, 1};
   double best_t = 1e30;
-  for (int gw : {4, 2, 1}) {
-    if (ng % gw != 0) continue;
-    const long ngb = ng / gw;
-    for (int split = 1; split <= std::min(16, ks); ++split) {
-      const long wgs = (ngb * split + 3) / 4, rounds = (wgs + cus - 1) / cus;
-      const double t = 0.146 * rounds * (gw + 0.25 * mb) * ((ks + split - 1) / split) +
-                       2.0 * split * M * (double)N * 4 / 8e6;
+  for (int gw = 1; gw <= (mb == 1 ? 5 : 4); ++gw) {
+    const long ngb = (ng + gw - 1) / gw;
+    const double rate = gw * mb == 2 || gw * mb == 1 || gw >= 3 ? 36e3 : 29e3;  // bytes per us
+    for (int split = 1; split <= (epi == EPI_RESID ? std::min(8, ks) : 1); ++split) {
+      const long rounds = (ngb * split + cus - 1) / cus;
+      const double cu = rounds * (gw + 0.33 * mb) * 1024.0 * ((ks + split - 1) / split);
+      const double t_w = 2.0 * N * K / 6.9e6, t_cu = cu / rate;
+      const double t = 3.0 * rounds + std::max(t_w, t_cu) + 0.25 * std::min(t_w, t_cu) +
+                       (split > 1 ? 8.0 * split * M * (double)N / 8e6 : 0.0);
       if (t < best_t - 1e-9) {
         best_t = t;
         best = RowsPlan{gw, split};
@@ -1510,66 +1616,70 @@ void launch_pack_gemm_weights(const GemmArgs& g, bf16_t* out, hipStream_t s) {
   DLLM_LAUNCH_CHECK("pack_gemm_weights");
 }
 
-// launches the register-direct kernel can take (given the packed copy)
-bool rows_path(int M, int N, int K) { return M >= 1 && M <= 64 && N % 32 == 0 && K % 64 == 0; }
+bool gemm_rows_path(int M) { return M >= 1 && M <= GEMM_ROWS_MAX; }
 
 size_t gemm_bf16_splitk_bytes(int M, int N, int K, int epi) {
   const Plan p = plan(M, N, K, epi);
   size_t b = p.split > 1 ? (size_t)p.split * M * N * sizeof(float) : 0;
   const WdPlan wp = wd_plan(M, N, K, epi);  // with packed weights
   if (wp.tile && wp.split > 1) b = std::max(b, (size_t)wp.split * M * N * sizeof(float));
-  if (rows_path(M, N, K)) b = std::max(b, (size_t)rows_plan(M, N, K).split * M * N * sizeof(float));
+  if (gemm_rows_path(M)) {
+    const int split = rows_plan(M, N, K, epi).split;
+    if (split > 1) b = std::max(b, (size_t)split * M * N * sizeof(float));
+  }
   return b;
 }
 
-template <int S>
-void launch_splitk_resid(const float* part, float* resid, long MN, hipStream_t s) {
-  hipLaunchKernelGGL(splitk_resid_kernel<S>, dim3(ceil_div(MN / 4, 256)), dim3(256), 0, s, part, resid, MN);
+// resid += the S partials [S, MN], S = 1 .. 16
+void launch_splitk(const float* part, float* resid, long MN, int split, hipStream_t s) {
+  auto go = [&](auto sc) {
+    hipLaunchKernelGGL(splitk_resid_kernel<decltype(sc)::value>, dim3(ceil_div(MN / 4, 256)), dim3(256), 0, s, part,
+                       resid, MN);
+  };
+  switch (split) {
+#define DLLM_CASE(S_) \
+  case S_: go(std::integral_constant<int, S_>{}); break;
+    DLLM_CASE(2) DLLM_CASE(3) DLLM_CASE(4) DLLM_CASE(5) DLLM_CASE(6) DLLM_CASE(7) DLLM_CASE(8) DLLM_CASE(9)
+    DLLM_CASE(10) DLLM_CASE(11) DLLM_CASE(12) DLLM_CASE(13) DLLM_CASE(14) DLLM_CASE(15) DLLM_CASE(16)
+#undef DLLM_CASE
+    default: throw HipError("splitk_resid: split must be 2 .. 16");
+  }
+  DLLM_LAUNCH_CHECK("splitk_resid");
 }
 
-// The register-direct path: partials from gemm_rows_kernel, then the epilogue.
-// A residual GEMM's partials are left to the next norm when defer is given
-// (its 1024-thread fused kernel adds them), else reduced across the chip.
+template <int EPI, int GW, int MB>
+void launch_rows_tile(const GemmArgs& a, int split, hipStream_t s) {
+  using RT = RowsTile<GW, MB>;
+  static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_rows_kernel<EPI, GW, MB>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)RT::LDS);
+  hip_check(attr, "hipFuncSetAttribute(gemm_rows)");
+  hipLaunchKernelGGL((gemm_rows_kernel<EPI, GW, MB>), dim3(ceil_div(a.N / 32, GW) * split), dim3(64 * RT::NW), RT::LDS,
+                     s, a, split);
+}
+
+// The path of at most 64 rows.  A split residual GEMM's partials are left to the
+// next norm when defer is given, else reduced across the chip.
+template <int EPI>
 void launch_gemm_rows(const GemmArgs& a, hipStream_t s, PendingResid* defer) {
-  const RowsPlan rp = rows_plan(a.M, a.N, a.K);
-  RowsArgs r{a.A, a.Wp, a.splitk_buf, a.M, a.N, a.K, rp.split, a.N / 32 / rp.gw};
-  const dim3 grid(ceil_div(r.ngb * r.S, 4)), blk(256);
-  const bool two = a.M > 32;
+  if (EPI == EPI_SWIGLU && !a.outf) throw HipError("gemm_rows: SwiGLU needs its operand-order output");
+  const RowsPlan rp = rows_plan(a.M, a.N, a.K, EPI);
   auto go = [&](auto gwc) {
     constexpr int GW = decltype(gwc)::value;
-    if (two)
-      hipLaunchKernelGGL((gemm_rows_kernel<GW, 2, 4>), grid, blk, 0, s, r);
-    else
-      hipLaunchKernelGGL((gemm_rows_kernel<GW, 1, 8>), grid, blk, 0, s, r);
+    a.M > 32 ? launch_rows_tile<EPI, GW, 2>(a, rp.split, s) : launch_rows_tile<EPI, GW, 1>(a, rp.split, s);
   };
-  if (rp.gw == 4)
-    go(std::integral_constant<int, 4>{});
-  else if (rp.gw == 2)
-    go(std::integral_constant<int, 2>{});
-  else
-    go(std::integral_constant<int, 1>{});
-  DLLM_LAUNCH_CHECK("gemm_rows");
-  if (a.epi == EPI_SWIGLU) {
-    const long n = (long)a.M * (a.N / 2);
-    hipLaunchKernelGGL(splitk_swiglu_kernel, dim3(ceil_div(n, 256)), dim3(256), 0, s, a.splitk_buf, rp.split, a.M,
-                       a.N / 2, a.out);
-  } else if (a.epi == EPI_QKV_ROPE) {
-    const long n = (long)a.M * a.N;
-    hipLaunchKernelGGL(splitk_qkv_kernel, dim3(ceil_div(n, 256)), dim3(256), 0, s, a.splitk_buf, rp.split, a);
-  } else if (defer && a.M <= RESID_NORM_WIDE_ROWS) {
-    *defer = PendingResid{a.splitk_buf, rp.split};
-  } else {
-    const long MN = (long)a.M * a.N;
-    switch (rp.split) {
-#define DLLM_CASE(S_) \
-  case S_: launch_splitk_resid<S_>(a.splitk_buf, a.resid, MN, s); break;
-      DLLM_CASE(1) DLLM_CASE(2) DLLM_CASE(3) DLLM_CASE(4) DLLM_CASE(5) DLLM_CASE(6) DLLM_CASE(7) DLLM_CASE(8)
-      DLLM_CASE(9) DLLM_CASE(10) DLLM_CASE(11) DLLM_CASE(12) DLLM_CASE(13) DLLM_CASE(14) DLLM_CASE(15) DLLM_CASE(16)
-#undef DLLM_CASE
-      default: throw HipError("gemm_rows: split must be 1 .. 16");
-    }
+  switch (rp.gw) {
+    case 1: go(std::integral_constant<int, 1>{}); break;
+    case 2: go(std::integral_constant<int, 2>{}); break;
+    case 3: go(std::integral_constant<int, 3>{}); break;
+    case 4: go(std::integral_constant<int, 4>{}); break;
+    default: launch_rows_tile<EPI, 5, 1>(a, rp.split, s); break;  // at most 32 rows
   }
-  DLLM_LAUNCH_CHECK("gemm_rows epilogue");
+  DLLM_LAUNCH_CHECK("gemm_rows");
+  if (EPI != EPI_RESID || rp.split == 1) return;
+  if (defer)
+    *defer = PendingResid{a.splitk_buf, rp.split};
+  else
+    launch_splitk(a.splitk_buf, a.resid, (long)a.M * a.N, rp.split, s);
 }
 
 template <class TL, int EPI>
@@ -1592,8 +1702,14 @@ void launch_gemm_bf16(const GemmArgs& a, hipStream_t s, PendingResid* defer) {
     throw HipError("gemm_bf16: q/k/v epilogue needs B * L < 2^24 and B < 2^16");
   if (a.epi == EPI_QKV_ROPE && (a.Lq < 1 || a.pos0 < 0 || a.pos0 + a.Lq > a.L || a.M % a.Lq != 0))
     throw HipError("gemm_bf16: q/k/v rows must be whole windows of Lq positions inside the sequence");
-  if (a.Wp && rows_path(a.M, a.N, a.K)) {  // few rows from the packed copy: register-direct
-    launch_gemm_rows(a, s, defer);
+  if (a.Wp && gemm_rows_path(a.M)) {  // few rows from the packed copy: register-direct
+    if (!a.Af || a.N % 32 != 0) throw HipError("gemm_rows: needs A in operand order and N % 32 == 0");
+    switch (a.epi) {
+      case EPI_QKV_ROPE: launch_gemm_rows<EPI_QKV_ROPE>(a, s, defer); break;
+      case EPI_SWIGLU: launch_gemm_rows<EPI_SWIGLU>(a, s, defer); break;
+      case EPI_RESID: launch_gemm_rows<EPI_RESID>(a, s, defer); break;
+      default: throw HipError("gemm_rows: unknown epilogue");
+    }
     return;
   }
   const WdPlan wp = a.Wp ? wd_plan(a.M, a.N, a.K, a.epi) : WdPlan{0, 1};
@@ -1614,15 +1730,7 @@ void launch_gemm_bf16(const GemmArgs& a, hipStream_t s, PendingResid* defer) {
     if (wp.split > 1 && defer) {
       *defer = PendingResid{a.splitk_buf, wp.split};  // the next norm adds them
     } else if (wp.split > 1) {
-      const long MN = (long)a.M * a.N;
-      switch (wp.split) {
-#define DLLM_CASE(S_) \
-  case S_: launch_splitk_resid<S_>(a.splitk_buf, a.resid, MN, s); break;
-        DLLM_CASE(2) DLLM_CASE(3) DLLM_CASE(4) DLLM_CASE(5) DLLM_CASE(6) DLLM_CASE(7) DLLM_CASE(8)
-#undef DLLM_CASE
-        default: throw HipError("gemm_wd: split must be 1 .. 8");
-      }
-      DLLM_LAUNCH_CHECK("splitk_resid");
+      launch_splitk(a.splitk_buf, a.resid, (long)a.M * a.N, wp.split, s);
     }
     return;
   }
@@ -1648,30 +1756,7 @@ void launch_gemm_bf16(const GemmArgs& a, hipStream_t s, PendingResid* defer) {
     // fused reduce + norm runs one workgroup per row
     *defer = PendingResid{a.splitk_buf, p.split};
   } else if (p.split > 1) {
-    const long MN = (long)a.M * a.N;
-    const dim3 grid(ceil_div(MN / 4, 256));
-    auto go = [&](auto sc) {
-      hipLaunchKernelGGL(splitk_resid_kernel<decltype(sc)::value>, grid, dim3(256), 0, s, a.splitk_buf, a.resid, MN);
-    };
-    switch (p.split) {
-      case 2: go(std::integral_constant<int, 2>{}); break;
-      case 3: go(std::integral_constant<int, 3>{}); break;
-      case 4: go(std::integral_constant<int, 4>{}); break;
-      case 5: go(std::integral_constant<int, 5>{}); break;
-      case 6: go(std::integral_constant<int, 6>{}); break;
-      case 7: go(std::integral_constant<int, 7>{}); break;
-      case 8: go(std::integral_constant<int, 8>{}); break;
-      case 9: go(std::integral_constant<int, 9>{}); break;
-      case 10: go(std::integral_constant<int, 10>{}); break;
-      case 11: go(std::integral_constant<int, 11>{}); break;
-      case 12: go(std::integral_constant<int, 12>{}); break;
-      case 13: go(std::integral_constant<int, 13>{}); break;
-      case 14: go(std::integral_constant<int, 14>{}); break;
-      case 15: go(std::integral_constant<int, 15>{}); break;
-      case 16: go(std::integral_constant<int, 16>{}); break;
-      default: throw HipError("splitk_resid: split must be 2 .. 16");
-    }
-    DLLM_LAUNCH_CHECK("splitk_resid");
+    launch_splitk(a.splitk_buf, a.resid, (long)a.M * a.N, p.split, s);
   }
 }
 

@@ -213,13 +213,13 @@ void launch_rmsnorm_t(const float* h, const TG* g, TO* out, int B, int rows, int
 // rmsnorm_vec_kernel preceded by the split-K residual update of its row: each
 // float4 of the row is h + ((p_0 + p_1) + ... + p_{S-1}), the same operations in
 // the same order as splitk_resid_kernel, written back to h and kept for the norm.
-// NT threads per row: 256, or 1024 for a few rows (a cached step's block
-// rows, whose register-direct GEMMs leave up to 16 partials): one workgroup per
-// row then has every partial load of the row in flight at once.
+// NT threads per row: 256, or 1024 for a few rows (a cached step's block rows;
+// S = 0: nothing pending), which then also go to an operand-order copy.
 template <int NV, int S, int NT = 256>
 __global__ void __launch_bounds__(NT) resid_rmsnorm_kernel(float* __restrict__ h, const float* __restrict__ part,
                                                            long MN, const bf16_t* __restrict__ g,
-                                                           bf16_t* __restrict__ out, int d, float eps) {
+                                                           bf16_t* __restrict__ out, bf16_t* __restrict__ outf, int d,
+                                                           float eps) {
   const int r = blockIdx.x;
   float* row = h + (size_t)r * d;
   const int d4 = d / 4;
@@ -229,22 +229,24 @@ __global__ void __launch_bounds__(NT) resid_rmsnorm_kernel(float* __restrict__ h
   for (int j = 0; j < NV; ++j) {
     const int c = threadIdx.x + NT * j;
     if (c < d4) {
-      const size_t i = (size_t)r * d4 + c;
-      float4 acc = reinterpret_cast<const float4*>(part)[i];
-#pragma unroll
-      for (int z = 1; z < S; ++z) {
-        const float4 p = reinterpret_cast<const float4*>(part + (size_t)z * MN)[i];
-        acc.x += p.x;
-        acc.y += p.y;
-        acc.z += p.z;
-        acc.w += p.w;
-      }
       float4 x = Vec4<float>::load(row, c);
-      x.x += acc.x;
-      x.y += acc.y;
-      x.z += acc.z;
-      x.w += acc.w;
-      Vec4<float>::store(row, c, x);
+      if (S > 0) {
+        const size_t i = (size_t)r * d4 + c;
+        float4 acc = reinterpret_cast<const float4*>(part)[i];
+#pragma unroll
+        for (int z = 1; z < S; ++z) {
+          const float4 p = reinterpret_cast<const float4*>(part + (size_t)z * MN)[i];
+          acc.x += p.x;
+          acc.y += p.y;
+          acc.z += p.z;
+          acc.w += p.w;
+        }
+        x.x += acc.x;
+        x.y += acc.y;
+        x.z += acc.z;
+        x.w += acc.w;
+        Vec4<float>::store(row, c, x);
+      }
       v[j] = x;
       ss += (double)x.x * x.x + (double)x.y * x.y + (double)x.z * x.z + (double)x.w * x.w;
     }
@@ -269,33 +271,35 @@ __global__ void __launch_bounds__(NT) resid_rmsnorm_kernel(float* __restrict__ h
     const int c = threadIdx.x + NT * j;
     if (c < d4) {
       const float4 gg = Vec4<bf16_t>::load(g, c);
-      Vec4<bf16_t>::store(dst, c, make_float4(v[j].x * rstd * gg.x, v[j].y * rstd * gg.y, v[j].z * rstd * gg.z,
-                                              v[j].w * rstd * gg.w));
+      const float4 y = make_float4(v[j].x * rstd * gg.x, v[j].y * rstd * gg.y, v[j].z * rstd * gg.z,
+                                   v[j].w * rstd * gg.w);
+      Vec4<bf16_t>::store(dst, c, y);
+      if (NT == 1024) Vec4<bf16_t>::store(outf + frag_at(((int)gridDim.x + 31) >> 5, r, 4 * c), 0, y);
     }
   }
 }
 
-void launch_resid_rmsnorm(float* h, const PendingResid& pend, const bf16_t* g, bf16_t* out, int M, int d, float eps,
-                          hipStream_t s) {
+void launch_resid_rmsnorm(float* h, const PendingResid& pend, const bf16_t* g, bf16_t* out, bf16_t* outf, int M, int d,
+                          float eps, hipStream_t s) {
   if (M == 0) return;
-  if (d % 4 != 0 || d > 8192 || ((uintptr_t)h | (uintptr_t)pend.part | (uintptr_t)g | (uintptr_t)out) % 16 != 0)
+  if (d % 4 != 0 || d > 8192 ||
+      ((uintptr_t)h | (uintptr_t)pend.part | (uintptr_t)g | (uintptr_t)out | (uintptr_t)outf) % 16 != 0)
     throw HipError("resid_rmsnorm: needs d % 4 == 0, d <= 8192 and 16-byte aligned rows");
   const long MN = (long)M * d;
   // the split count is a template parameter so that every partial's loads are in flight at once
-  if (M <= RESID_NORM_WIDE_ROWS) {
+  if (outf) {
+    if (M > GEMM_ROWS_MAX || d % 16 != 0) throw HipError("resid_rmsnorm: operand order holds 64 rows of whole slices");
     auto go = [&](auto nvc, auto sc) {
       hipLaunchKernelGGL((resid_rmsnorm_kernel<decltype(nvc)::value, decltype(sc)::value, 1024>), dim3(M), dim3(1024),
-                         0, s, h, pend.part, MN, g, out, d, eps);
+                         0, s, h, pend.part, MN, g, out, outf, d, eps);
     };
     auto by_split = [&](auto nvc) {
       switch (pend.split) {
 #define DLLM_CASE(S_) \
   case S_: go(nvc, std::integral_constant<int, S_>{}); break;
-        DLLM_CASE(1) DLLM_CASE(2) DLLM_CASE(3) DLLM_CASE(4) DLLM_CASE(5) DLLM_CASE(6) DLLM_CASE(7) DLLM_CASE(8)
-        DLLM_CASE(9) DLLM_CASE(10) DLLM_CASE(11) DLLM_CASE(12) DLLM_CASE(13) DLLM_CASE(14) DLLM_CASE(15)
-        DLLM_CASE(16)
+        DLLM_CASE(0) DLLM_CASE(2) DLLM_CASE(3) DLLM_CASE(4) DLLM_CASE(5) DLLM_CASE(6) DLLM_CASE(7) DLLM_CASE(8)
 #undef DLLM_CASE
-        default: throw HipError("resid_rmsnorm: split must be 1 .. 16");
+        default: throw HipError("resid_rmsnorm: split must be 0 or 2 .. 8");
       }
     };
     if (d <= 4096)
@@ -308,7 +312,7 @@ void launch_resid_rmsnorm(float* h, const PendingResid& pend, const bf16_t* g, b
   const int nv = ceil_div(d, 1024);
   auto go = [&](auto nvc, auto sc) {
     hipLaunchKernelGGL((resid_rmsnorm_kernel<decltype(nvc)::value, decltype(sc)::value>), dim3(M), dim3(256), 0, s, h,
-                       pend.part, MN, g, out, d, eps);
+                       pend.part, MN, g, out, outf, d, eps);
   };
   auto by_split = [&](auto nvc) {
     switch (pend.split) {

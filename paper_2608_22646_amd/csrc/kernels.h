@@ -69,6 +69,9 @@ struct GemmArgs {
   int epi;
   int M, N, K;              // N counts output columns of the virtual B (gate and up both counted)
   const bf16_t* A;          // [M, K]
+  // launches of at most GEMM_ROWS_MAX rows with Wp set: A in operand order
+  // (frag_at), and for EPI_SWIGLU a second, operand-order output
+  const bf16_t* Af; bf16_t* outf;
   const bf16_t* W0;         // q / gate / plain weight [*, K]
   const bf16_t* W1;         // k / up
   const bf16_t* W2;         // v
@@ -84,13 +87,20 @@ struct GemmArgs {
   int B, L, Hq, Hkv, Lq, pos0;
   // split-K scratch (float32 partials [split, M, N]) from the workspace
   float* splitk_buf;
-  // optional packed copy of Bv (launch_pack_gemm_weights): launches of at most
-  // 128 rows then stream it instead of the row-major tensors
+  // optional packed copy of Bv (launch_pack_gemm_weights)
   const bf16_t* Wp;
   // EPI_QKV_ROPE: error word; a v value beyond IEEE half's range is stored as
   // +-65504 and sets ERR_V_RANGE
   int* err;
 };
+// Rows up to which a GEMM with packed weights streams them register-direct; its
+// producers then also write A in MFMA operand order: element (m, k) of [M, K] at
+// frag_at(MB, m, k), MB = 32-row blocks (rows past M are never stored from).
+constexpr int GEMM_ROWS_MAX = 64;
+bool gemm_rows_path(int M);
+__host__ __device__ inline size_t frag_at(int MB, int m, int k) {
+  return ((size_t)(k >> 4) * MB + (m >> 5)) * 512 + ((m & 31) + 32 * ((k >> 3) & 1)) * 8 + (k & 7);
+}
 int device_cu_count();  // compute units of the current device (256 if it cannot be queried)
 // Split-K partial tiles of a residual GEMM whose reduction into the residual
 // has been left to the next RMSNorm (split 0: nothing pending).
@@ -98,20 +108,18 @@ struct PendingResid {
   const float* part = nullptr;  // [split, M, N] float32
   int split = 0;
 };
-// With defer non-null, a split-K residual GEMM of more than 128 rows leaves its
-// partials pending there instead of launching the reduction (defer->split = 0
-// otherwise).
+// With defer non-null, a split-K residual GEMM of more than 128 rows, or of the
+// few-row path, leaves its partials pending there instead of launching the
+// reduction (defer->split = 0 otherwise).
 void launch_gemm_bf16(const GemmArgs& a, hipStream_t s, PendingResid* defer = nullptr);
 // Completes a deferred residual update and normalises in one pass, for every
 // row m < M (bf16 model, d % 4 == 0, d <= 8192):
 //   h[m, :] += sum_z part[z, m, :]   (z in order, as the split-K reduction does)
 //   out[m, :] = bf16(RMSNorm(h[m, :]) * g)
-// Rows up to which the split-K partials of the register-direct GEMM (1 .. 16
-// of them) are left pending for the next norm, and the fused kernel runs one
-// 1024-thread workgroup per row (d <= 8192).
-constexpr int RESID_NORM_WIDE_ROWS = 64;
-void launch_resid_rmsnorm(float* h, const PendingResid& pend, const bf16_t* g, bf16_t* out, int M, int d, float eps,
-                          hipStream_t s);
+// With outf (M <= GEMM_ROWS_MAX) the normed rows also go there in operand order;
+// such launches run one 1024-thread workgroup per row, and pend may be empty.
+void launch_resid_rmsnorm(float* h, const PendingResid& pend, const bf16_t* g, bf16_t* out, bf16_t* outf, int M, int d,
+                          float eps, hipStream_t s);
 // Packed copy of a GEMM's virtual weight matrix (g's W0/W1/W2, n0, n1, N, K,
 // epi) in the LM head's tiled operand order, rows padded to 256.
 size_t gemm_packed_bytes(int N, int K);
@@ -124,9 +132,10 @@ size_t gemm_bf16_splitk_bytes(int M, int N, int K, int epi);
 // out[b*Lq + l, h*128 + j] (bf16).  With split_part (attn_split_bytes(B, Hq)
 // bytes) and split_ticket (B * Hq ints, zero; left zero) a launch of at most 32
 // queries per sequence splits the keys of each head over several workgroups.
+// With outf (B * Lq <= GEMM_ROWS_MAX) the rows also go there in operand order.
 size_t attn_split_bytes(int B, int Hq);
-void launch_attn_bf16(const bf16_t* q, const bf16_t* k, const f16_t* vt, bf16_t* out, int B, int Lq, int L, int Hq,
-                      int Hkv, hipStream_t s, float* split_part = nullptr, int* split_ticket = nullptr);
+void launch_attn_bf16(const bf16_t* q, const bf16_t* k, const f16_t* vt, bf16_t* out, bf16_t* outf, int B, int Lq,
+                      int L, int Hq, int Hkv, hipStream_t s, float* split_part = nullptr, int* split_ticket = nullptr);
 
 // The bf16 LM head is read from a tiled copy: vocabulary tiles of HEAD_TILE rows,
 // each stored as d/64 consecutive [HEAD_TILE, 64] blocks, rows past V zero;

@@ -1,0 +1,71 @@
+"""The few-row GEMM (packed weights, at most 64 rows) at the edges of its plans.
+
+Every stage of a layer against the oracle (gpu_stages), at widths whose 32-row
+groups divide into every group count a workgroup takes, leave remainders, or
+give some waves no slice of K; one and two row operands, whole and partial; the
+attention kernels that write its operand-order input; and the split residual
+sums folded into the next norm against the separate reduction.
+"""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_stages import check_layer, check_layer_cached
+from paper_2608_22646_amd import binding as B
+from paper_2608_22646_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def model_of(d, heads, kv, ff, layers=1):
+    cfg = synth.ModelConfig("rows-edge", n_layers=layers, d_model=d, n_heads=heads, n_kv_heads=kv, head_dim=128,
+                            d_ff=ff, vocab=1000, rope_base=10000.0, dtype="bf16", lm_head_std=5 / math.sqrt(d),
+                            norm_gain_std=0.1)
+    w = synth.make_weights(cfg, "cpu")
+    return cfg, B.Model(cfg, [t.cuda() for t in w]).pack_weights(), [t.to(torch.float32).numpy() for t in w]
+
+
+# (d, heads, kv heads, d_ff): 256 = eight groups, one 16-k slice per wave; 2304 =
+# 72 groups; d_ff 18944 = 1184 gate/up groups (five a workgroup at 32 rows)
+SHAPES = [(256, 2, 2, 128), (2304, 18, 2, 1408), (3584, 28, 4, 18944)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("Bn,L", [(1, 2), (1, 30), (2, 18), (1, 64)])
+def test_full_forward_of_few_rows(gpu_lib, shape, Bn, L):
+    cfg, model, w = model_of(*shape)
+    ws = model.workspace(Bn, L, min(L, 32))
+    model.embed(synth.make_ints((Bn, L), 3, 0, cfg.vocab).cuda(), ws)
+    check_layer(model, cfg, w, ws, Bn, L, 0)
+
+
+@pytest.mark.parametrize("shape", SHAPES[1:])
+@pytest.mark.parametrize("Bn,L,row0,rows", [(1, 78, 40, 32), (3, 50, 9, 16), (1, 200, 101, 64), (2, 96, 64, 32)])
+def test_cached_rows(gpu_lib, shape, Bn, L, row0, rows):
+    cfg, model, w = model_of(*shape)
+    kv, ws = model.kv_cache(Bn, L), model.workspace(Bn, L, rows)
+    x = synth.make_ints((Bn, L), 4, 0, cfg.vocab).cuda()
+    model.embed(x, ws)
+    model.layer_kv(0, 2, Bn, L, 0, L, kv, ws)
+    model.embed_rows(x.flip(1).contiguous(), row0, rows, ws)
+    check_layer_cached(model, cfg, w, ws, kv, Bn, L, row0, rows, 0)
+
+
+@pytest.mark.parametrize("rows", [5, 32, 64])
+def test_folded_residual_sums_equal_the_reduction(gpu_lib, rows):
+    cfg, model, _ = model_of(3584, 28, 4, 1408, layers=2)
+    L, row0 = 130, 40
+    x = synth.make_ints((1, L), 6, 0, cfg.vocab).cuda()
+    kv, ws = model.kv_cache(1, L), model.workspace(1, L, rows)
+    model.forward_kv(x, row0, rows, kv, refresh=True, ws=ws)
+    kv2 = B.device_buffer(kv.numel()).copy_(kv)
+    _, _, fused = model.forward_kv(x, row0, rows, kv, refresh=False, ws=ws, logits=True)
+    model.embed_rows(x, row0, rows, ws)
+    for l in range(cfg.n_layers):
+        model.layer_kv(l, 2, 1, L, row0, rows, kv2, ws)
+    h = ws[model.layout(1, L, rows).h:][:rows * cfg.d_model * 4].view(torch.float32).view(rows, -1).clone()
+    _, _, calls = model.head_noalloc(h, 1, rows, 0, rows, logits=True)
+    assert torch.equal(fused.view(torch.int32), calls.view(torch.int32))
+    assert torch.equal(kv, kv2)
