@@ -797,20 +797,37 @@ __global__ void __launch_bounds__(64 * QG * KGRP, 1) attn_kv4_kernel(const bf16_
 // Key-split variant for at most 32 queries per (sequence, head) -- a cached
 // step's block rows against every cached position: the keys of a head are
 // split over NS workgroups of NWS waves, wave w of split s taking the 32-key
-// tiles s nt / NS + w, + NWS, ... (nt tiles in all).  With one query group a
-// tile is read by exactly one wave, so its K and V^T fragments go straight
-// from memory into registers (the next tile's loads in flight under the
-// current one's MFMAs): no LDS ring and no barrier in the loop.  The waves'
-// running (max, sum, output) states are merged in wave order through LDS; with
-// NS > 1 the workgroup publishes the merged state (device-coherent stores) and
-// takes a ticket of its (sequence, head), and the last of the NS workgroups
-// merges the NS states in split order (wave w the output dimensions 32 w ..),
-// writes the bf16 rows and re-arms the ticket.  Tickets start at zero (the
-// forward's embedding kernel clears them) and every launch leaves them zero.
+// tiles tb + w, + NWS, .. of the split's range, with no barrier in the loop.  A
+// tile belongs to one wave: its K rows come in by LDS-DMA (1 KiB of whole rows an
+// instruction) into the wave's own two-slot ring, its V^T fragments straight
+// into registers, the next tile's K in flight under the whole of the current one
+// and its V^T under the scores and the softmax.
+// (K fragments loaded straight into registers touch 32 cache lines for 32
+// bytes each an instruction, four times the lines of a tile through a 32 KiB
+// L1 that four waves' tiles overflow: 13.7 us at 32 heads x 512 keys and 41 us
+// at 28 heads x 8257 keys, against 10.5 and 27.7 here; 35 us at 256 heads x 1024
+// keys either way, 3.9 TB/s.  Non-temporal loads were slower, 44 us there.)
+//
+// V^T rows start at any multiple of two bytes: with ODD (L odd) a lane whose
+// row starts at an odd element loads the aligned dwords around its eight keys
+// and shifts them into place; the last dword of a head's V^T is aligned, so its
+// last key stays inside the buffer bound.
+//
+// The waves' running (max, sum, output) states meet in LDS, each wave finishing
+// its share of the output dimensions in wave order; with NS > 1 the workgroup
+// publishes the merged state (device-coherent stores) and takes a ticket of its
+// (sequence, head), and the last of the NS workgroups merges the NS states in
+// split order, writes the bf16 rows and re-arms the ticket.  Tickets start at
+// zero (the forward's embedding kernel clears them) and every launch leaves
+// them zero.
 constexpr int CPOL_SC1_A = 16;  // cache-policy bit: coherent at device (agent) scope
 constexpr int SPLIT_STATE = 17 * 64 * 16;  // bytes of one published state: 16 float4 of o + (m, l) per lane
-
 template <int NWS>
+constexpr size_t split_lds() {  // K rings, then the waves' states
+  return std::max((size_t)NWS * 2 * KB2, (size_t)NWS * SPLIT_STATE);
+}
+
+template <int NWS, bool ODD>
 __global__ void __launch_bounds__(64 * NWS, 1) attn_split_kernel(const bf16_t* __restrict__ q,
                                                                  const bf16_t* __restrict__ k,
                                                                  const f16_t* __restrict__ vt,
@@ -818,7 +835,7 @@ __global__ void __launch_bounds__(64 * NWS, 1) attn_split_kernel(const bf16_t* _
                                                                  int* __restrict__ ticket, int Lq, int L, int Hq,
                                                                  int Hkv, int NS) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  __shared__ float4 xch[NWS > 1 ? NWS - 1 : 1][17][64];
+  extern __shared__ __attribute__((aligned(16))) char lds[];
   __shared__ int last_flag;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // XCD-aware 1-D grid over (sequence, head, split), the splits of a head adjacent
@@ -833,21 +850,48 @@ __global__ void __launch_bounds__(64 * NWS, 1) attn_split_kernel(const bf16_t* _
   const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((void*)kh, 0, L * HD * 2, 0x00020000);
   const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void*)vh, 0, HD * L * 2, 0x00020000);
   typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-  // K operand i of a tile at key t0: key t0 + kperm(lq), dimensions 16 i + 8 half ..;
+  // K part i of a tile: keys 4 i + l/16, slot l%16 holding chunk (l%16) ^ (key & 15)
+  uint32_t ko[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int key = 4 * i + (lane >> 4);
+    ko[i] = (uint32_t)(key * 256 + (((lane & 15) ^ (key & 15)) << 4));
+  }
   // V^T operand (jk, ds): dimension 32 ds + lq, keys t0 + 16 jk + 8 half ..
-  const uint32_t ko = (uint32_t)((kperm(lq) * HD + half * 8) * 2), vo = (uint32_t)((lq * L + half * 8) * 2);
-  u32x4_t kb[2][8], vb[2][8];
-  auto load = [&](int t, int set) {
+  const uint32_t vo = (uint32_t)((lq * L + half * 8) * 2) & ~3u;
+  const uint32_t shift = ODD && (lq & 1) ? 16 : 0;  // bits past the aligned dword where the row starts
+  char* ring = lds + wave * (2 * KB2);
+  u32x4_t vb[8];
+  uint32_t vx[8];
+  constexpr int VOPS = ODD ? 16 : 8;  // V^T loads of one tile
+  auto load_k = [&](int t, int set) {
     const int t0 = t * KT2;
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      kb[set][i] = __builtin_amdgcn_raw_buffer_load_b128(rk, ko + (uint32_t)((t0 * HD + 16 * i) * 2), 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lds_ptr_t)(ring + set * KB2 + i * 1024), 16,
+                                               ko[i & 3] + (uint32_t)(t0 * 256 + (i >> 2) * 4096), 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto load_v = [&](int t) {
+    __builtin_amdgcn_sched_barrier(0);
+    const int t0 = t * KT2;
 #pragma unroll
     for (int jk = 0; jk < 2; ++jk)
 #pragma unroll
-      for (int ds = 0; ds < 4; ++ds)
-        vb[set][jk * 4 + ds] =
-            __builtin_amdgcn_raw_buffer_load_b128(rv, vo + (uint32_t)((ds * 32 * L + t0 + 16 * jk) * 2), 0, 0);
+      for (int ds = 0; ds < 4; ++ds) {
+        const uint32_t o = vo + (uint32_t)((ds * 32 * L + t0 + 16 * jk) * 2);
+        vb[jk * 4 + ds] = __builtin_amdgcn_raw_buffer_load_b128(rv, o, 0, 0);
+        if (ODD) vx[jk * 4 + ds] = __builtin_amdgcn_raw_buffer_load_b32(rv, o + 16, 0, 0);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto vfrag = [&](int i) {
+    u32x4_t v = vb[i];
+    if (ODD) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = __builtin_amdgcn_alignbit(e < 3 ? vb[i][e + 1] : vx[i], vb[i][e], shift);
+    }
+    return __builtin_bit_cast(f16x8_t, v);
   };
 
   bf16x8_t qf[8];
@@ -868,20 +912,29 @@ __global__ void __launch_bounds__(64 * NWS, 1) attn_split_kernel(const bf16_t* _
   float m_run = -INFINITY, l_run = 0.f;
   const float sc = 1.4426950408889634f / sqrtf((float)HD);
 
-  // one 32-key tile from fragment set S_ (compile-time), the next tile's
-  // fragments loading into the other set meanwhile
+  // one 32-key tile from ring slot `cur` (compile-time); the next tile's K loads
+  // into the other slot meanwhile, its V^T as soon as this tile's is used (past
+  // the split's last tile: that tile again, never used, so that the wait always
+  // counts the V^T of this tile and the K of the next as issued after its K)
   auto step = [&](int t, auto set_c) {
     constexpr int cur = decltype(set_c)::value;
-    if (t + NWS < te) load(t + NWS, cur ^ 1);
+    const int tn = min(t + NWS, te - 1);
+    asm volatile("" ::: "memory");  // the slot's last readers are done (their MFMAs waited for them)
+    load_k(tn, cur ^ 1);
+    wait_vmcnt_a<VOPS + 8>();
+    asm volatile("" ::: "memory");
+    const char* base = ring + cur * KB2;
     const int t0 = t * KT2;
+    bf16x8_t kf[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) kf[i] = *reinterpret_cast<const bf16x8_t*>(base + k_off(kperm(lq), 2 * i + half));
     f32x16_t s2, s2b;
 #pragma unroll
     for (int r = 0; r < 16; ++r) s2[r] = s2b[r] = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; i += 2) {
-      s2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kb[cur][i]), qf[i], s2, 0, 0, 0);
-      s2b = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kb[cur][i + 1]), qf[i + 1], s2b, 0,
-                                                    0, 0);
+      s2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i], qf[i], s2, 0, 0, 0);
+      s2b = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i + 1], qf[i + 1], s2b, 0, 0, 0);
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r) s2[r] += s2b[r];
@@ -923,94 +976,96 @@ __global__ void __launch_bounds__(64 * NWS, 1) attn_split_kernel(const bf16_t* _
       for (int e = 0; e < 8; ++e) pf[e] = (_Float16)s2[jk * 8 + e];
 #pragma unroll
       for (int ds = 0; ds < 4; ++ds)
-        o[ds] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, vb[cur][jk * 4 + ds]), pf, o[ds],
-                                                       0, 0, 0);
+        o[ds] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vfrag(jk * 4 + ds), pf, o[ds], 0, 0, 0);
     }
+    load_v(tn);
   };
   int t = tb + wave;
-  if (t < te) load(t, 0);
-  while (t < te) {
-    step(t, std::integral_constant<int, 0>{});
-    t += NWS;
-    if (t >= te) break;
-    step(t, std::integral_constant<int, 1>{});
-    t += NWS;
+  if (t < te) {
+    load_k(t, 0);
+    load_v(t);
+    while (true) {
+      step(t, std::integral_constant<int, 0>{});
+      t += NWS;
+      if (t >= te) break;
+      step(t, std::integral_constant<int, 1>{});
+      t += NWS;
+      if (t >= te) break;
+    }
   }
 
-  // merge the waves in wave order; a wave that saw no key (m = -inf) adds nothing
-  if (NWS > 1) {
-    if (wave > 0) {
+  // every wave leaves its state: 16 float4 units (output dimensions 32 (u / 4) +
+  // 8 (u % 4) + 4 half .. of query lq), then (m, l); wave w finishes units w, w +
+  // NWS, .. over the waves in wave order (a wave that saw no key, m = -inf, adds
+  // nothing)
+  wait_vmcnt_a<0>();  // the loads past the last tile have landed
+  __syncthreads();
+  {
+    float4* x = reinterpret_cast<float4*>(lds) + (size_t)wave * (17 * 64) + lane;
 #pragma unroll
-      for (int ds = 0; ds < 4; ++ds)
+    for (int ds = 0; ds < 4; ++ds)
 #pragma unroll
-        for (int rq = 0; rq < 4; ++rq)
-          xch[wave - 1][ds * 4 + rq][lane] =
-              make_float4(o[ds][4 * rq], o[ds][4 * rq + 1], o[ds][4 * rq + 2], o[ds][4 * rq + 3]);
-      xch[wave - 1][16][lane] = make_float4(m_run, l_run, 0.f, 0.f);
+      for (int rq = 0; rq < 4; ++rq)
+        x[(ds * 4 + rq) * 64] = make_float4(o[ds][4 * rq], o[ds][4 * rq + 1], o[ds][4 * rq + 2], o[ds][4 * rq + 3]);
+    x[16 * 64] = make_float4(m_run, l_run, 0.f, 0.f);
+  }
+  __syncthreads();
+  constexpr int UW = 16 / NWS;  // units per wave
+  float4 acc[UW];
+  float m = -INFINITY, l = 0.f;
+  {
+    const float4* x = reinterpret_cast<const float4*>(lds) + lane;
+    float a[NWS];
+#pragma unroll
+    for (int e = 0; e < NWS; ++e) m = fmaxf(m, x[(e * 17 + 16) * 64].x);
+#pragma unroll
+    for (int e = 0; e < NWS; ++e) {
+      const float4 ml = x[(e * 17 + 16) * 64];
+      a[e] = ml.x == -INFINITY ? 0.f : exp2_hw(ml.x - m);
+      l += ml.y * a[e];
     }
-    __syncthreads();
-    if (wave == 0) {
-      float m = m_run;
 #pragma unroll
-      for (int e = 0; e < NWS - 1; ++e) m = fmaxf(m, xch[e][16][lane].x);
-      const float a0 = m_run == -INFINITY ? 0.f : exp2_hw(m_run - m);
-      l_run *= a0;
+    for (int i = 0; i < UW; ++i) {
+      acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-      for (int ds = 0; ds < 4; ++ds)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[ds][r] *= a0;
-#pragma unroll
-      for (int e = 0; e < NWS - 1; ++e) {
-        const float me = xch[e][16][lane].x, le = xch[e][16][lane].y;
-        const float ae = me == -INFINITY ? 0.f : exp2_hw(me - m);
-        l_run += le * ae;
-#pragma unroll
-        for (int ds = 0; ds < 4; ++ds)
-#pragma unroll
-          for (int rq = 0; rq < 4; ++rq) {
-            const float4 v = xch[e][ds * 4 + rq][lane];
-            o[ds][4 * rq] += v.x * ae;
-            o[ds][4 * rq + 1] += v.y * ae;
-            o[ds][4 * rq + 2] += v.z * ae;
-            o[ds][4 * rq + 3] += v.w * ae;
-          }
+      for (int e = 0; e < NWS; ++e) {
+        const float4 v = x[(e * 17 + wave + NWS * i) * 64];
+        acc[i].x += v.x * a[e];
+        acc[i].y += v.y * a[e];
+        acc[i].z += v.z * a[e];
+        acc[i].w += v.w * a[e];
       }
-      m_run = m;
     }
   }
-
-  auto store_rows = [&](const f32x16_t* oo, int ds0, int nds, float l) {
-    const float inv = 1.0f / sum_pair32(l);
+  auto store_units = [&](float lsum) {
+    const float inv = 1.0f / sum_pair32(lsum);
     if (lq >= Lq) return;
-    for (int ds = ds0; ds < ds0 + nds; ++ds)
 #pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        const int d = ds * 32 + 8 * rg + 4 * half;
-        uint2 w;
-        w.x = pack_bf16x2(oo[ds - ds0][rg * 4 + 0] * inv, oo[ds - ds0][rg * 4 + 1] * inv);
-        w.y = pack_bf16x2(oo[ds - ds0][rg * 4 + 2] * inv, oo[ds - ds0][rg * 4 + 3] * inv);
-        out.store4((size_t)b * Lq + lq, h, d, w);
-      }
+    for (int i = 0; i < UW; ++i) {
+      const int u = wave + NWS * i, d = 32 * (u >> 2) + 8 * (u & 3) + 4 * half;
+      out.store4((size_t)b * Lq + lq, h, d,
+                 make_uint2(pack_bf16x2(acc[i].x * inv, acc[i].y * inv), pack_bf16x2(acc[i].z * inv, acc[i].w * inv)));
+    }
   };
   if (NS == 1) {
-    if (wave == 0) store_rows(o, 0, 4, l_run);
+    store_units(l);
     return;
   }
 
   // publish the workgroup's state: lane-contiguous float4s [17][64] per (sequence, head, split)
   const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((void*)part, 0, 0x7fffffff, 0x00020000);
-  if (wave == 0) {
+  {
     const uint32_t base = (uint32_t)(((size_t)bh * NS + s) * SPLIT_STATE) + lane * 16;
 #pragma unroll
-    for (int ds = 0; ds < 4; ++ds)
-#pragma unroll
-      for (int rq = 0; rq < 4; ++rq) {
-        const u32x4_t v = {__float_as_uint(o[ds][4 * rq]), __float_as_uint(o[ds][4 * rq + 1]),
-                           __float_as_uint(o[ds][4 * rq + 2]), __float_as_uint(o[ds][4 * rq + 3])};
-        __builtin_amdgcn_raw_buffer_store_b128(v, rp, base + (ds * 4 + rq) * 1024, 0, CPOL_SC1_A);
-      }
-    const u32x4_t ml = {__float_as_uint(m_run), __float_as_uint(l_run), 0u, 0u};
-    __builtin_amdgcn_raw_buffer_store_b128(ml, rp, base + 16 * 1024, 0, CPOL_SC1_A);
+    for (int i = 0; i < UW; ++i) {
+      const u32x4_t v = {__float_as_uint(acc[i].x), __float_as_uint(acc[i].y), __float_as_uint(acc[i].z),
+                         __float_as_uint(acc[i].w)};
+      __builtin_amdgcn_raw_buffer_store_b128(v, rp, base + (wave + NWS * i) * 1024, 0, CPOL_SC1_A);
+    }
+    if (wave == 0) {
+      const u32x4_t ml = {__float_as_uint(m), __float_as_uint(l), 0u, 0u};
+      __builtin_amdgcn_raw_buffer_store_b128(ml, rp, base + 16 * 1024, 0, CPOL_SC1_A);
+    }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
@@ -1018,45 +1073,44 @@ __global__ void __launch_bounds__(64 * NWS, 1) attn_split_kernel(const bf16_t* _
   __syncthreads();
   if (!last_flag) return;
 
-  // last workgroup of the head: wave w merges output dimensions 32 ds .. 32 ds
-  // + 31, ds = w, w + NWS, .., of every split in split order (the merged m first)
-  for (int ds = wave; ds < 4; ds += NWS) {
-    // the splits' states in rounds of ZB, all loads of a round in flight at
-    // once; an online merge in split order (the running max raised, the
-    // accumulated rows rescaled)
-    constexpr int ZB = 4;
-    float m = -INFINITY, l = 0.f;
-    f32x16_t acc;
+  // last workgroup of the head: an online merge in split order (the running max
+  // raised, the accumulated units rescaled), the splits' states in rounds of ZB
+  // with all loads of a round in flight at once
+  constexpr int ZB = 4;
+  m = -INFINITY;
+  l = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    for (int z0 = 0; z0 < NS; z0 += ZB) {
-      u32x4_t ml[ZB], ov[ZB][4];
+  for (int i = 0; i < UW; ++i) acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int z0 = 0; z0 < NS; z0 += ZB) {
+    u32x4_t ml[ZB], ov[ZB][UW];
 #pragma unroll
-      for (int j = 0; j < ZB; ++j) {
-        const int z = min(z0 + j, NS - 1);
-        const uint32_t base = (uint32_t)(((size_t)bh * NS + z) * SPLIT_STATE) + lane * 16;
-        ml[j] = __builtin_amdgcn_raw_buffer_load_b128(rp, base + 16 * 1024, 0, CPOL_SC1_A);
+    for (int j = 0; j < ZB; ++j) {
+      const int z = min(z0 + j, NS - 1);
+      const uint32_t base = (uint32_t)(((size_t)bh * NS + z) * SPLIT_STATE) + lane * 16;
+      ml[j] = __builtin_amdgcn_raw_buffer_load_b128(rp, base + 16 * 1024, 0, CPOL_SC1_A);
 #pragma unroll
-        for (int rq = 0; rq < 4; ++rq)
-          ov[j][rq] = __builtin_amdgcn_raw_buffer_load_b128(rp, base + (ds * 4 + rq) * 1024, 0, CPOL_SC1_A);
-      }
+      for (int i = 0; i < UW; ++i)
+        ov[j][i] = __builtin_amdgcn_raw_buffer_load_b128(rp, base + (wave + NWS * i) * 1024, 0, CPOL_SC1_A);
+    }
 #pragma unroll
-      for (int j = 0; j < ZB; ++j) {
-        if (z0 + j >= NS) break;
-        const float mz = __uint_as_float(ml[j][0]);
-        if (mz == -INFINITY) continue;  // a split that saw no key adds nothing
-        const float mn = fmaxf(m, mz);
-        const float ar = m == -INFINITY ? 0.f : exp2_hw(m - mn), az = exp2_hw(mz - mn);
-        m = mn;
-        l = l * ar + __uint_as_float(ml[j][1]) * az;
+    for (int j = 0; j < ZB; ++j) {
+      if (z0 + j >= NS) break;
+      const float mz = __uint_as_float(ml[j][0]);
+      if (mz == -INFINITY) continue;  // a split that saw no key adds nothing
+      const float mn = fmaxf(m, mz);
+      const float ar = m == -INFINITY ? 0.f : exp2_hw(m - mn), az = exp2_hw(mz - mn);
+      m = mn;
+      l = l * ar + __uint_as_float(ml[j][1]) * az;
 #pragma unroll
-        for (int rq = 0; rq < 4; ++rq)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[4 * rq + e] = acc[4 * rq + e] * ar + __uint_as_float(ov[j][rq][e]) * az;
+      for (int i = 0; i < UW; ++i) {
+        acc[i].x = acc[i].x * ar + __uint_as_float(ov[j][i][0]) * az;
+        acc[i].y = acc[i].y * ar + __uint_as_float(ov[j][i][1]) * az;
+        acc[i].z = acc[i].z * ar + __uint_as_float(ov[j][i][2]) * az;
+        acc[i].w = acc[i].w * ar + __uint_as_float(ov[j][i][3]) * az;
       }
     }
-    store_rows(&acc, ds, 1, l);
   }
+  store_units(l);
   if (tid == 0) ticket[bh] = 0;
 #endif
 }
@@ -1071,20 +1125,27 @@ void launch_attn_bf16(const bf16_t* q, const bf16_t* k, const f16_t* vt, bf16_t*
   if (outf && B * Lq > GEMM_ROWS_MAX) throw HipError("attn: the operand-order output holds 64 rows");
   const AttnOut out{out_rows, outf, ceil_div(B * Lq, 32), Hq};
   if (Lq <= QW && split_part && split_ticket) {
-    // one query group per head: the keys split over NS workgroups of 4 waves
-    // when that fills 7/8 of the CUs, else of 2 waves (shorter sequences)
     const long bh = (long)B * Hq, cus = std::min(device_cu_count(), 512);
     const int nt = (L + KT2 - 1) / KT2;
-    auto splits = [&](int nws) { return (int)std::max(1L, std::min<long>(cus / bh, (nt + nws - 1) / nws)); };
-    const int ns4 = splits(4);
-    if (8 * bh * ns4 >= 7 * cus || ns4 == 1) {
-      hipLaunchKernelGGL(attn_split_kernel<4>, dim3(bh * ns4), dim3(256), 0, s, q, k, vt, out, split_part,
-                         split_ticket, Lq, L, Hq, Hkv, ns4);
-    } else {
-      const int ns2 = splits(2);
-      hipLaunchKernelGGL(attn_split_kernel<2>, dim3(bh * ns2), dim3(128), 0, s, q, k, vt, out, split_part,
-                         split_ticket, Lq, L, Hq, Hkv, ns2);
-    }
+    auto go = [&](auto nwc, auto oddc, int ns) {
+      constexpr int NWS = decltype(nwc)::value;
+      constexpr bool ODD = decltype(oddc)::value;
+      static const hipError_t at = hipFuncSetAttribute((const void*)attn_split_kernel<NWS, ODD>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                       (int)split_lds<NWS>());
+      hip_check(at, "hipFuncSetAttribute(attn_split)");
+      hipLaunchKernelGGL((attn_split_kernel<NWS, ODD>), dim3(bh * ns), dim3(64 * NWS), split_lds<NWS>(), s, q, k, vt,
+                         out, split_part, split_ticket, Lq, L, Hq, Hkv, ns);
+    };
+    auto by_odd = [&](auto nwc, int ns) {
+      L % 2 ? go(nwc, std::true_type{}, ns) : go(nwc, std::false_type{}, ns);
+    };
+    // as many splits as fit the CUs with at least four tiles each, on eight waves
+    // (32 heads, 512 keys: 10.5 us at 4 splits, 12.5 at 2, 14.2 at 1; at 8 splits
+    // of four waves 11.8; 28 heads, 8257 keys: 27.7 at 9, 40 at 4), on four when
+    // the heads alone fill them (256 heads, 1024 keys: 34.7 against 36.2)
+    const int ns = (int)std::max(1L, std::min<long>(cus / bh, nt / 4));
+    ns == 1 ? by_odd(std::integral_constant<int, 4>{}, ns) : by_odd(std::integral_constant<int, 8>{}, ns);
     DLLM_LAUNCH_CHECK("attn_split");
     return;
   }
