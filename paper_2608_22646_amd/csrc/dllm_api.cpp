@@ -77,6 +77,7 @@ struct Layout {
   size_t part_m, part_s, part_i, ticket, hbf;    // bf16 head
   size_t splitk;                                 // bf16 split-K GEMM partials
   size_t attn_part, attn_ticket;                 // bf16 key-split attention states and tickets
+  size_t vpad;                                   // bf16, L % 8 != 0: V^T with padded rows
   size_t af, of, uf;                             // bf16, few rows: normed rows, attention output, u in operand order
   size_t conf, argmax, all_done, err;            // step scratch
   size_t total;
@@ -115,6 +116,7 @@ Layout make_layout(const dllm_model_cfg& c, int B, int L, int rows) {
     o.hbf = take((size_t)HEAD_FRAG_ROWS * d * 2);
     o.attn_ticket = take((size_t)B * c.n_heads * 4);
     o.attn_part = take(attn_split_bytes(B, c.n_heads));
+    o.vpad = take(attn_pad_bytes(B, c.n_kv_heads, L));
     const size_t fr = std::min<size_t>((M + 31) / 32 * 32, GEMM_ROWS_MAX);
     o.af = take(fr * d * 2);
     o.of = take(fr * c.n_heads * hd * 2);
@@ -353,7 +355,8 @@ void run_layer_bf16(const dllm_model* m, int layer, int part, int B, int L, void
     {
       ProfScope p(m, PK_ATTN, s);
       launch_attn_bf16(g.q, g.k, g.vt, at<bf16_t>(ws, lay.attn), of, B, Lq, L, c.n_heads, c.n_kv_heads, s,
-                       at<float>(ws, lay.attn_part), at<int>(ws, lay.attn_ticket));
+                       at<float>(ws, lay.attn_part), at<int>(ws, lay.attn_ticket),
+                       L % 8 ? at<f16_t>(ws, lay.vpad) : nullptr);
     }
     GemmArgs o = layer_gemm(m, layer, 1);
     o.M = M;

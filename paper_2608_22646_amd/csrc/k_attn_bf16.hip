@@ -3,19 +3,22 @@
 //
 //   out[b, l, h*128 + j] = sum_k softmax_k(q[b,h,l,:] . k[b,g(h),k,:] / sqrt(128)) v[b,g(h),k,j]
 //
-// Every query attends to every key (no mask); g(h) = h / (Hq / Hkv).
-// Workgroup = 4 wavefronts = 128 queries of one (sequence, head); wave w owns
-// 32 queries.  Keys stream through LDS in tiles of 64 (K [64][128] and
-// V^T [128][64], double buffered).  Per tile a wave computes
-//   S^T (64 keys x 32 queries) = K . Q^T      (16 MFMAs, Q held in registers)
+// Every query attends to every key (no mask); g(h) = h / (Hq / Hkv).  A wave
+// owns 32 queries of one (sequence, head).  Per key tile it computes
+//   S^T (keys x 32 queries) = K . Q^T      (Q held in registers)
 // so that each lane holds scores of a single query: the row max needs one
 // cross-lane exchange (lane ^ 32) and the rescale factor is per lane.  Then
-//   O^T (128 x 32) += V^T . P^T               (16 MFMAs)
+//   O^T (128 x 32) += V^T . P^T
 // in IEEE half: P in [0, 1] rounded to half (11-bit significand, 8x finer than
 // bf16) and V^T holding the bf16 values of v, which half represents exactly in
 // its range.  The K rows of the S^T product are fed in a permuted order inside
 // each 16-key group (kperm), so the scores a lane holds for one P.V slice are
-// 8 consecutive keys and its V^T operand is a single 16-byte LDS read.
+// 8 consecutive keys and its V^T operand is a single 16-byte piece.
+//
+// Three kernels: attn_stream_kernel (long launches), attn_kv4_kernel (launches
+// that would leave CUs idle), attn_split_kernel (at most 32 queries per
+// sequence).  The first two copy V^T rows to LDS in 16-byte pieces: at lengths
+// that are no multiple of 8 they read a copy with padded rows.
 #include <algorithm>
 #include <type_traits>
 
@@ -25,7 +28,7 @@ namespace dllm {
 
 namespace {
 
-constexpr int HD = 128, KT = 64, QW = 32, NW = 4;
+constexpr int HD = 128, KT = 64, QW = 32;
 
 // 2^x by the hardware instruction alone (v_exp_f32), without libm's rescaling
 // for results below 2^-126: every argument here is a score minus a running
@@ -95,175 +98,15 @@ __device__ __forceinline__ float sum_pair32(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-__global__ void __launch_bounds__(256, 1) attn_bf16_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
-                                                           const f16_t* __restrict__ vt, AttnOut out, int Lq, int L,
-                                                           int Hq, int Hkv) {
-  extern __shared__ __attribute__((aligned(16))) char lds[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int3 wb = attn_block((Lq + QW * NW - 1) / (QW * NW), Hq);
-  const int h = wb.y, b = wb.z, g = h / (Hq / Hkv);
-  const int q0 = wb.x * (QW * NW) + wave * QW;
-  const int lq = lane & 31, half = lane >> 5;
-  const bf16_t* kh = k + ((size_t)b * Hkv + g) * L * HD;
-  const f16_t* vh = vt + ((size_t)b * Hkv + g) * HD * L;
-
-  // Q as the B operand: lane holds query q0 + lq, dims 16*ks + 8*half .. +7.
-  bf16x8_t qf[8];
-  {
-    const int qi = q0 + lq;
-    const bf16_t* qrow = q + (((size_t)b * Hq + h) * Lq + (qi < Lq ? qi : 0)) * HD;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      qf[ks] = *reinterpret_cast<const bf16x8_t*>(qrow + ks * 16 + half * 8);
-      if (qi >= Lq) qf[ks] = bf16x8_t{0, 0, 0, 0, 0, 0, 0, 0};
-    }
-  }
-
-  // tile loader: 4 x 16 B of K and 4 x 16 B of V^T per thread
-  uint4 rk[4], rv[4];
-  auto gload = [&](int t0) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = tid + 256 * i;
-      const int key = e >> 4, ch = e & 15;  // K: 64 rows x 16 chunks
-      const int gk = t0 + key;
-      rk[i] = gk < L ? *reinterpret_cast<const uint4*>(kh + (size_t)gk * HD + ch * 8) : make_uint4(0, 0, 0, 0);
-      const int d = e >> 3, vc = e & 7;     // V^T: 128 rows x 8 chunks
-      const int gv = t0 + vc * 8;
-      if ((L & 7) == 0 && gv + 8 <= L) {
-        rv[i] = *reinterpret_cast<const uint4*>(vh + (size_t)d * L + gv);
-      } else {
-        uint16_t tmp[8];
-        for (int x = 0; x < 8; ++x) tmp[x] = (gv + x < L) ? vh[(size_t)d * L + gv + x] : (uint16_t)0;
-        rv[i] = *reinterpret_cast<uint4*>(tmp);
-      }
-    }
-  };
-  auto sstore = [&](int buf) {
-    char* base = lds + buf * STAGE;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = tid + 256 * i;
-      *reinterpret_cast<uint4*>(base + k_off(e >> 4, e & 15)) = rk[i];
-      *reinterpret_cast<uint4*>(base + v_off(e >> 3, e & 7)) = rv[i];
-    }
-  };
-
-  f32x16_t o[4];
-#pragma unroll
-  for (int ds = 0; ds < 4; ++ds)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[ds][r] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-  const float sc = 1.4426950408889634f / sqrtf((float)HD);  // log2(e) / sqrt(hd)
-
-  const int ntiles = (L + KT - 1) / KT;
-  gload(0);
-  sstore(0);
-  __syncthreads();
-  for (int t = 0; t < ntiles; ++t) {
-    const int buf = t & 1;
-    if (t + 1 < ntiles) gload((t + 1) * KT);
-    const char* base = lds + buf * STAGE;
-
-    // S^T = K . Q^T for keys 32*st + (rows), queries = lanes; the K fragments
-    // are read ahead of their MFMAs
-    f32x16_t s[2];
-    bf16x8_t kf[2][8];
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks)
-        kf[st][ks] = *reinterpret_cast<const bf16x8_t*>(base + k_off(st * 32 + kperm(lq), ks * 2 + half));
-#pragma unroll
-    for (int st = 0; st < 2; ++st) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[st][r] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) s[st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[st][ks], qf[ks], s[st], 0, 0, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-    for (int x = 0; x < 8; ++x) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-    // scale into the log2 domain, mask keys past L, tile max
-    const int t0 = t * KT;
-    float mt = -INFINITY;
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = t0 + st * 32 + kperm(8 * (r >> 2) + 4 * half + (r & 3));
-        const float x = key < L ? s[st][r] * sc : -INFINITY;
-        s[st][r] = x;
-        mt = fmaxf(mt, x);
-      }
-    mt = max_pair32(mt);
-    const float m_new = fmaxf(m_run, mt);
-    const float alpha = exp2_hw(m_run - m_new);
-    m_run = m_new;
-    float psum = 0.f;
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float p = exp2_hw(s[st][r] - m_new);
-        s[st][r] = p;
-        psum += p;
-      }
-    l_run = l_run * alpha + psum;
-#pragma unroll
-    for (int ds = 0; ds < 4; ++ds)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[ds][r] *= alpha;
-
-    // O^T += V^T . P^T over four 16-key slices
-#pragma unroll
-    for (int jk = 0; jk < 4; ++jk) {
-      f16x8_t pf;
-      const int st = jk >> 1, r0 = (jk & 1) * 8;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) pf[e] = (_Float16)s[st][r0 + e];
-      // slot e: key 16jk + 8*half + e (kperm), one 16-byte V^T chunk
-#pragma unroll
-      for (int ds = 0; ds < 4; ++ds) {
-        const int d = ds * 32 + lq;
-        const f16x8_t vf = *reinterpret_cast<const f16x8_t*>(base + v_off(d, 2 * jk + half));
-        o[ds] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pf, o[ds], 0, 0, 0);
-      }
-    }
-    if (t + 1 < ntiles) sstore(buf ^ 1);
-    __syncthreads();
-  }
-
-  const float l_tot = sum_pair32(l_run);
-  const float inv = 1.0f / l_tot;
-  const int qi = q0 + lq;
-  if (qi >= Lq) return;
-#pragma unroll
-  for (int ds = 0; ds < 4; ++ds)
-#pragma unroll
-    for (int rg = 0; rg < 4; ++rg) {
-      const int d = ds * 32 + 8 * rg + 4 * half;
-      uint2 w;
-      w.x = pack_bf16x2(o[ds][rg * 4 + 0] * inv, o[ds][rg * 4 + 1] * inv);
-      w.y = pack_bf16x2(o[ds][rg * 4 + 2] * inv, o[ds][rg * 4 + 3] * inv);
-      out.store4((size_t)b * Lq + qi, h, d, w);
-    }
-}
-
-
 // ---------------------------------------------------------------------------
-// Streaming variant for sequences whose length is a multiple of 8: NW
-// wavefronts x 32 queries per workgroup (NW = 8: two waves per SIMD, so one
+// Streaming variant: NW wavefronts x 32 queries per workgroup (NW = 8: two waves per SIMD, so one
 // wave's softmax overlaps the other's MFMAs, and each K/V tile serves 256
 // queries).  K and V^T tiles are copied straight into a 3-stage LDS ring with
 // buffer_load_dwordx4 ... lds.  Keys past L are masked; their K rows read as
 // zero through the buffer bound, and their V^T columns hold either the next
-// d-row's (finite) values or, past the end of the head, zeros.  The 1/sqrt(hd) * log2(e) scale is folded into the
-// exp2 argument, and the running maximum is only raised when a tile's maximum
+// d-row's (finite) values or, in the padding of a padded copy and past the end of
+// the head, zeros.  LV is the stride of V^T rows (a multiple of 8).  The 1/sqrt(hd)
+// * log2(e) scale is folded into the exp2 argument, and the running maximum is only raised when a tile's maximum
 // exceeds it by more than 8 (log2 units): unnormalised probabilities then stay
 // below 2^8 (exact to half's relative precision) and the O / l rescale is
 // skipped for most tiles.
@@ -284,7 +127,7 @@ template <int NW>
 __global__ void __launch_bounds__(64 * NW, 1) attn_stream_kernel(const bf16_t* __restrict__ q,
                                                                  const bf16_t* __restrict__ k,
                                                                  const f16_t* __restrict__ vt,
-                                                                 AttnOut out, int Lq, int L, int Hq, int Hkv) {
+                                                                 AttnOut out, int Lq, int L, int LV, int Hq, int Hkv) {
 #if defined(__HIP_DEVICE_COMPILE__)
   // D tiles in flight ahead of the one in use
   constexpr int D = 2, S = D + 1, PER_STAGE = 32 / NW;  // 16 K + 16 V^T DMA instructions per tile
@@ -295,7 +138,7 @@ __global__ void __launch_bounds__(64 * NW, 1) attn_stream_kernel(const bf16_t* _
   const int q0 = wb.x * (QW * NW) + wave * QW;
   const int lq = lane & 31, half = lane >> 5;
   const bf16_t* kh = k + ((size_t)b * Hkv + g) * L * HD;
-  const f16_t* vh = vt + ((size_t)b * Hkv + g) * HD * L;
+  const f16_t* vh = vt + ((size_t)b * Hkv + g) * HD * LV;
 
   bf16x8_t qf[8];
   {
@@ -313,7 +156,7 @@ __global__ void __launch_bounds__(64 * NW, 1) attn_stream_kernel(const bf16_t* _
   // fills d rows 8i..8i+7 (rows of 128 B, lane l -> d = 8i + l/8, slot l%8
   // holding chunk (l%8) ^ ((d >> 1) & 7)).  Wave w issues instructions w, w + NW, ...
   const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((void*)kh, 0, L * HD * 2, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void*)vh, 0, HD * L * 2, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void*)vh, 0, HD * LV * 2, 0x00020000);
   constexpr int PK = 16 / NW;
   uint32_t vok[PK], vov[PK];
 #pragma unroll
@@ -322,7 +165,7 @@ __global__ void __launch_bounds__(64 * NW, 1) attn_stream_kernel(const bf16_t* _
     const int key = 4 * i + (lane >> 4), kc = (lane & 15) ^ (key & 15);
     vok[j] = (uint32_t)((key * HD + kc * 8) * 2);
     const int d = 8 * i + (lane >> 3), vc = (lane & 7) ^ ((d >> 1) & 7);
-    vov[j] = (uint32_t)(((size_t)d * L + vc * 8) * 2);
+    vov[j] = (uint32_t)(((size_t)d * LV + vc * 8) * 2);
   }
   auto issue = [&](int t) {
     char* base = lds + (t % S) * STAGE;
@@ -492,7 +335,7 @@ template <int QG>
 __global__ void __launch_bounds__(64 * QG * KGRP, 1) attn_kv4_kernel(const bf16_t* __restrict__ q,
                                                                     const bf16_t* __restrict__ k,
                                                                     const f16_t* __restrict__ vt,
-                                                                    AttnOut out, int Lq, int L, int Hq, int Hkv) {
+                                                                    AttnOut out, int Lq, int L, int LV, int Hq, int Hkv) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int NW = QG * KGRP, S = 2;
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -503,7 +346,7 @@ __global__ void __launch_bounds__(64 * QG * KGRP, 1) attn_kv4_kernel(const bf16_
   const int q0 = wb.x * (QW * QG) + qg * QW;
   const int lq = lane & 31, half = lane >> 5;
   const bf16_t* kh = k + ((size_t)b * Hkv + g) * L * HD;
-  const f16_t* vh = vt + ((size_t)b * Hkv + g) * HD * L;
+  const f16_t* vh = vt + ((size_t)b * Hkv + g) * HD * LV;
 
   // DMA of a step: 64 instructions of 1 KiB, instruction j (tile j / 16,
   // part j % 16) issued by wave j % NW.  K part i < 8: keys 4i + l/16, slot
@@ -511,7 +354,7 @@ __global__ void __launch_bounds__(64 * QG * KGRP, 1) attn_kv4_kernel(const bf16_
   // 16 (i - 8) + l/4, slot l%4 holding chunk (l%4) ^ ((d >> 2) & 3).  Reads
   // past the end of this head's K or V^T return zeros (buffer bound).
   const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((void*)kh, 0, L * HD * 2, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void*)vh, 0, HD * L * 2, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void*)vh, 0, HD * LV * 2, 0x00020000);
   constexpr int PJ = (64 + NW - 1) / NW;
   uint32_t voff[PJ];
 #pragma unroll
@@ -522,7 +365,7 @@ __global__ void __launch_bounds__(64 * QG * KGRP, 1) attn_kv4_kernel(const bf16_
       voff[x] = (uint32_t)((key * HD + kc * 8) * 2);
     } else {
       const int d = 16 * (part - 8) + (lane >> 2), vc = (lane & 3) ^ ((d >> 2) & 3);
-      voff[x] = (uint32_t)(((size_t)d * L + vc * 8) * 2);
+      voff[x] = (uint32_t)(((size_t)d * LV + vc * 8) * 2);
     }
   }
   auto issue = [&](int u) {
@@ -1115,16 +958,51 @@ __global__ void __launch_bounds__(64 * NWS, 1) attn_split_kernel(const bf16_t* _
 #endif
 }
 
+// vt rows of L values -> rows of LV = L rounded up to 8, the padding zero.  One
+// thread per eight values: a source row starts at any multiple of two bytes, so
+// the aligned dwords around them are loaded and shifted into place.
+__global__ void __launch_bounds__(256) pad_vt_kernel(const f16_t* __restrict__ vt, f16_t* __restrict__ out, int rows,
+                                                     int L, int LV) {
+  const int per = LV / 8;
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (long)rows * per) return;
+  const int r = (int)(i / per), c = (int)(i - (long)r * per);
+  const long e0 = (long)r * L + 8 * c;
+  uint32_t w[5];
+  if (8 * c + 8 <= L) {
+    const uint32_t* p = reinterpret_cast<const uint32_t*>(vt) + (e0 >> 1);
+    const bool odd = e0 & 1;
+    __builtin_memcpy(w, p, 16);
+    w[4] = odd ? p[4] : 0u;
+    if (odd) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = (w[e] >> 16) | (w[e + 1] << 16);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t lo = 8 * c + 2 * e < L ? vt[e0 + 2 * e] : 0, hi = 8 * c + 2 * e + 1 < L ? vt[e0 + 2 * e + 1] : 0;
+      w[e] = lo | (hi << 16);
+    }
+  }
+  *reinterpret_cast<uint4*>(out + (size_t)r * LV + 8 * c) = make_uint4(w[0], w[1], w[2], w[3]);
+}
+
 }  // namespace
+
+size_t attn_pad_bytes(int B, int Hkv, int L) {
+  return L % 8 ? (size_t)B * Hkv * HD * ((L + 7) / 8 * 8) * sizeof(f16_t) : 0;
+}
 
 size_t attn_split_bytes(int B, int Hq) { return (size_t)std::max(B * Hq, 512) * SPLIT_STATE; }
 
 void launch_attn_bf16(const bf16_t* q, const bf16_t* k, const f16_t* vt, bf16_t* out_rows, bf16_t* outf, int B, int Lq,
-                      int L, int Hq, int Hkv, hipStream_t s, float* split_part, int* split_ticket) {
+                      int L, int Hq, int Hkv, hipStream_t s, float* split_part, int* split_ticket, f16_t* pad) {
   if (B * Lq == 0) return;
   if (outf && B * Lq > GEMM_ROWS_MAX) throw HipError("attn: the operand-order output holds 64 rows");
   const AttnOut out{out_rows, outf, ceil_div(B * Lq, 32), Hq};
-  if (Lq <= QW && split_part && split_ticket) {
+  if (Lq <= QW) {
+    if (!split_part || !split_ticket) throw HipError("attn: few queries need the key-split buffers");
     const long bh = (long)B * Hq, cus = std::min(device_cu_count(), 512);
     const int nt = (L + KT2 - 1) / KT2;
     auto go = [&](auto nwc, auto oddc, int ns) {
@@ -1149,63 +1027,61 @@ void launch_attn_bf16(const bf16_t* q, const bf16_t* k, const f16_t* vt, bf16_t*
     DLLM_LAUNCH_CHECK("attn_split");
     return;
   }
-  if (L % 8 == 0) {
-    // streaming kernel: 8 waves (256 queries) per workgroup when that still gives
-    // two or more workgroups per CU over the launch, else 4 waves; when even the
-    // 4-wave grid leaves CUs without a workgroup, or there is only one 32-query
-    // group per (sequence, head), the key-split kernel (four waves per query over
-    // interleaved 32-key tiles)
-    const bool wide = (long)((Lq + 255) / 256) * Hq * B >= 512;
-    const size_t lds = 3 * (size_t)STAGE;
-    const long cus = device_cu_count();
-    if (Lq <= QW || ((long)((Lq + 127) / 128) * Hq * B < cus && L > KT)) {
-      // 32 queries per workgroup for a single query group, else 64 when that
-      // still fits the CUs, else 96
-      auto go = [&](auto qgc) {
-        constexpr int QG = decltype(qgc)::value;
-        // merge: every wave's state and the staged rows (up to 64 queries), or
-        // the three handed-over groups' states (96)
-        constexpr size_t ring = 2 * (size_t)STEP2,
-                         merge = QG <= 2 ? (size_t)QG * KGRP * 17 * 64 * 16 + (size_t)QG * QW * 272
-                                         : (size_t)3 * QG * 17 * 64 * 16;
-        constexpr size_t lds_kv = ring > merge ? ring : merge;
-        static const hipError_t a = hipFuncSetAttribute((const void*)attn_kv4_kernel<QG>,
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_kv);
-        hip_check(a, "hipFuncSetAttribute(attn_kv4)");
-        hipLaunchKernelGGL(attn_kv4_kernel<QG>, dim3(ceil_div(Lq, QW * QG) * Hq * B), dim3(64 * QG * KGRP), lds_kv, s,
-                           q, k, vt, out, Lq, L, Hq, Hkv);
-      };
-      if (Lq <= QW)
-        go(std::integral_constant<int, 1>{});
-      else if ((long)ceil_div(Lq, QW * 2) * Hq * B <= cus)
-        go(std::integral_constant<int, 2>{});
-      else
-        go(std::integral_constant<int, 3>{});
-      DLLM_LAUNCH_CHECK("attn_kv4");
-      return;
-    }
-    if (wide) {
-      static const hipError_t a8 =
-          hipFuncSetAttribute((const void*)attn_stream_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      hip_check(a8, "hipFuncSetAttribute(attn_stream<8>)");
-      hipLaunchKernelGGL(attn_stream_kernel<8>, dim3(ceil_div(Lq, QW * 8) * Hq * B), dim3(512), lds, s, q, k, vt, out,
-                         Lq, L, Hq, Hkv);
-    } else {
-      static const hipError_t a4 =
-          hipFuncSetAttribute((const void*)attn_stream_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      hip_check(a4, "hipFuncSetAttribute(attn_stream<4>)");
-      hipLaunchKernelGGL(attn_stream_kernel<4>, dim3(ceil_div(Lq, QW * 4) * Hq * B), dim3(256), lds, s, q, k, vt, out,
-                         Lq, L, Hq, Hkv);
-    }
-    DLLM_LAUNCH_CHECK("attn_stream");
+  // V^T rows of whole 16-byte pieces: a padded copy where L is no multiple of 8
+  // (the loads and stores of V once more, 5-6 us at 3 x 365 positions of 32 heads,
+  // where reading the ragged rows element by element took the attention 56 us)
+  const int LV = (L + 7) / 8 * 8;
+  if (LV != L) {
+    if (!pad) throw HipError("attn: lengths that are no multiple of 8 need the padded V^T buffer");
+    const int rows = B * Hkv * HD;
+    hipLaunchKernelGGL(pad_vt_kernel, dim3(ceil_div((long)rows * (LV / 8), 256)), dim3(256), 0, s, vt, pad, rows, L, LV);
+    DLLM_LAUNCH_CHECK("pad_vt");
+    vt = pad;
+  }
+  // streaming kernel: 8 waves (256 queries) per workgroup when that still gives
+  // two or more workgroups per CU over the launch, else 4 waves; when even the
+  // 4-wave grid leaves CUs without a workgroup, the key-group kernel (four waves
+  // per query over interleaved 32-key tiles)
+  const bool wide = (long)((Lq + 255) / 256) * Hq * B >= 512;
+  const size_t lds = 3 * (size_t)STAGE;
+  const long cus = device_cu_count();
+  if ((long)((Lq + 127) / 128) * Hq * B < cus && L > KT) {
+    // 64 queries per workgroup when that still fits the CUs, else 96
+    auto go = [&](auto qgc) {
+      constexpr int QG = decltype(qgc)::value;
+      // merge: every wave's state and the staged rows (up to 64 queries), or
+      // the three handed-over groups' states (96)
+      constexpr size_t ring = 2 * (size_t)STEP2,
+                       merge = QG <= 2 ? (size_t)QG * KGRP * 17 * 64 * 16 + (size_t)QG * QW * 272
+                                       : (size_t)3 * QG * 17 * 64 * 16;
+      constexpr size_t lds_kv = ring > merge ? ring : merge;
+      static const hipError_t a = hipFuncSetAttribute((const void*)attn_kv4_kernel<QG>,
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_kv);
+      hip_check(a, "hipFuncSetAttribute(attn_kv4)");
+      hipLaunchKernelGGL(attn_kv4_kernel<QG>, dim3(ceil_div(Lq, QW * QG) * Hq * B), dim3(64 * QG * KGRP), lds_kv, s,
+                         q, k, vt, out, Lq, L, LV, Hq, Hkv);
+    };
+    if ((long)ceil_div(Lq, QW * 2) * Hq * B <= cus)
+      go(std::integral_constant<int, 2>{});
+    else
+      go(std::integral_constant<int, 3>{});
+    DLLM_LAUNCH_CHECK("attn_kv4");
     return;
   }
-  static const hipError_t attr =
-      hipFuncSetAttribute((const void*)attn_bf16_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * STAGE);
-  hip_check(attr, "hipFuncSetAttribute(attn_bf16)");
-  hipLaunchKernelGGL(attn_bf16_kernel, dim3(ceil_div(Lq, QW * NW) * Hq * B), dim3(256), 2 * STAGE, s, q, k, vt, out, Lq,
-                     L, Hq, Hkv);
-  DLLM_LAUNCH_CHECK("attn_bf16");
+  if (wide) {
+    static const hipError_t a8 =
+        hipFuncSetAttribute((const void*)attn_stream_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hip_check(a8, "hipFuncSetAttribute(attn_stream<8>)");
+    hipLaunchKernelGGL(attn_stream_kernel<8>, dim3(ceil_div(Lq, QW * 8) * Hq * B), dim3(512), lds, s, q, k, vt, out,
+                       Lq, L, LV, Hq, Hkv);
+  } else {
+    static const hipError_t a4 =
+        hipFuncSetAttribute((const void*)attn_stream_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hip_check(a4, "hipFuncSetAttribute(attn_stream<4>)");
+    hipLaunchKernelGGL(attn_stream_kernel<4>, dim3(ceil_div(Lq, QW * 4) * Hq * B), dim3(256), lds, s, q, k, vt, out,
+                       Lq, L, LV, Hq, Hkv);
+  }
+  DLLM_LAUNCH_CHECK("attn_stream");
 }
 
 }  // namespace dllm

@@ -447,28 +447,26 @@ __device__ __forceinline__ void staged_store(const GemmArgs& g, const char* lds,
       const int rel = vb - nq - nkv;
       const int head = rel / HD, cj0 = rel % HD;
       constexpr int RC = BM / 8;  // 8-row chunks per column
-      for (int it = tid; it < 32 * RC; it += NTH) {
-        const int c = it / RC, t = it - c * RC, m = m0 + 8 * t;
-        if (m >= g.M) continue;
-        const uint4 val = *reinterpret_cast<const uint4*>(blk + c * St::VROW + 16 * t);
-        if (((g.L | g.Lq | g.pos0) & 7) == 0 && m + 7 < g.M) {
-          // eight positions of one sequence, 16-byte aligned (L, Lq, pos0 and m
-          // multiples of 8)
+      const bool whole = ((g.L | g.Lq | g.pos0) & 7) == 0;
+      if (whole)
+        for (int it = tid; it < 32 * RC; it += NTH) {
+          const int c = it / RC, t = it - c * RC, m = m0 + 8 * t;
+          if (m + 7 >= g.M) continue;  // M is a multiple of 8 as well
+          // eight positions of one sequence, 16-byte aligned
           const int2 bp = seq_pos(m, g.Lq, inv_l);
           const int b = bp.x, pos = g.pos0 + bp.y;
-          *reinterpret_cast<uint4*>(g.vt + (((size_t)b * g.Hkv + head) * HD + cj0 + c) * g.L + pos) = val;
-        } else {
-          const uint32_t wd[4] = {val.x, val.y, val.z, val.w};
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int mm = m + e;
-            if (mm >= g.M) break;
-            const int2 bp = seq_pos(mm, g.Lq, inv_l);
-            const int b = bp.x, pos = g.pos0 + bp.y;
-            g.vt[(((size_t)b * g.Hkv + head) * HD + cj0 + c) * g.L + pos] = (f16_t)(wd[e >> 1] >> (16 * (e & 1)));
-          }
+          *reinterpret_cast<uint4*>(g.vt + (((size_t)b * g.Hkv + head) * HD + cj0 + c) * g.L + pos) =
+              *reinterpret_cast<const uint4*>(blk + c * St::VROW + 16 * t);
         }
-      }
+      else  // one value per lane, positions along the lanes
+        for (int it = tid; it < 32 * BM; it += NTH) {
+          const int c = it / BM, r = it - c * BM, m = m0 + r;
+          if (m >= g.M) continue;
+          const int2 bp = seq_pos(m, g.Lq, inv_l);
+          const int b = bp.x, pos = g.pos0 + bp.y;
+          g.vt[(((size_t)b * g.Hkv + head) * HD + cj0 + c) * g.L + pos] =
+              *reinterpret_cast<const f16_t*>(blk + c * St::VROW + 2 * r);
+        }
     }
   }
 }

@@ -133,9 +133,13 @@ size_t gemm_bf16_splitk_bytes(int M, int N, int K, int epi);
 // bytes) and split_ticket (B * Hq ints, zero; left zero) a launch of at most 32
 // queries per sequence splits the keys of each head over several workgroups.
 // With outf (B * Lq <= GEMM_ROWS_MAX) the rows also go there in operand order.
+// Launches of more queries at an L that is no multiple of 8 need pad
+// (attn_pad_bytes(B, Hkv, L) bytes of scratch).
 size_t attn_split_bytes(int B, int Hq);
+size_t attn_pad_bytes(int B, int Hkv, int L);
 void launch_attn_bf16(const bf16_t* q, const bf16_t* k, const f16_t* vt, bf16_t* out, bf16_t* outf, int B, int Lq,
-                      int L, int Hq, int Hkv, hipStream_t s, float* split_part = nullptr, int* split_ticket = nullptr);
+                      int L, int Hq, int Hkv, hipStream_t s, float* split_part = nullptr, int* split_ticket = nullptr,
+                      f16_t* pad = nullptr);
 
 // The bf16 LM head is read from a tiled copy: vocabulary tiles of HEAD_TILE rows,
 // each stored as d/64 consecutive [HEAD_TILE, 64] blocks, rows past V zero;
