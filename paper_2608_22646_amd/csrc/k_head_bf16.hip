@@ -93,29 +93,35 @@ __device__ __forceinline__ size_t head_bf16_packed_bytes_dev(int V, int d) {
 // Statistics of one 32-row vocabulary group for head row `row` from the MFMA
 // result (lane holds vocabulary entries v0 + 8 (r/4) + 4 half + r%4, r < 16),
 // merged across the lane pair: valid in the half == 0 lane.  Writes the logits
-// too when a debug buffer is given.
+// too when a debug buffer is given.  Entries past V and the mask id become -inf
+// first, in the (wave-uniform) groups that hold any; then maximum, lowest index
+// at the maximum and sum of exponentials each take one short pass (tested and
+// tracked entry by entry, with exp2f's rescaling of results below 2^-126, a
+// 256 x 256 tile took ~8 us of a CU; such terms vanish beside a sum >= 1).
 template <bool LG = true>
 __device__ __forceinline__ Stat tile_stat(const HeadArgs& a, const f32x16_t& acc, int row, int v0, int half) {
+  auto entry = [&](int r) { return v0 + 8 * (r >> 2) + 4 * half + (r & 3); };
+  if (LG && a.logits && row < a.R) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (entry(r) < a.V) a.logits[(size_t)row * a.V + entry(r)] = acc[r];
+  }
+  f32x16_t x = acc;
+  if (v0 + 32 > a.V || (a.mask_id >= v0 && a.mask_id < v0 + 32)) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (entry(r) >= a.V || entry(r) == a.mask_id) x[r] = -INFINITY;
+  }
   Stat st{-INFINITY, 0.f, 0x7fffffff};
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int v = v0 + 8 * (r >> 2) + 4 * half + (r & 3);
-    const float x = acc[r];
-    if (LG && a.logits && row < a.R && v < a.V) a.logits[(size_t)row * a.V + v] = x;
-    if (v < a.V && v != a.mask_id && x > st.m) {
-      st.m = x;
-      st.i = v;
-    }
-  }
-  float s = 0.f;
+  for (int r = 0; r < 16; ++r) st.m = fmaxf(st.m, x[r]);
   if (st.m != -INFINITY) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int v = v0 + 8 * (r >> 2) + 4 * half + (r & 3);
-      if (v < a.V && v != a.mask_id) s += exp2f((acc[r] - st.m) * LOG2E);
-    }
+    for (int r = 15; r >= 0; --r)
+      if (x[r] == st.m) st.i = entry(r);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) st.s += __builtin_amdgcn_exp2f((x[r] - st.m) * LOG2E);
   }
-  st.s = s;
   Stat other;
   other.m = __shfl_xor(st.m, 32, 64);
   other.s = __shfl_xor(st.s, 32, 64);
@@ -396,26 +402,31 @@ __global__ void __launch_bounds__(256, 1) head_stream_kernel(HeadArgs a) {
 #endif
 }
 
-// Register-direct variant for more than 32 head rows (batched decodes): the
+// Register-direct variant for more than 64 head rows (batched decodes): the
 // workgroup tile is one 256-row vocabulary tile of the copy x all head rows
-// (up to 32 TI); wave w owns the tile's 32-row groups 2w and 2w + 1, whose
-// 1 KiB operands stream straight from the copy into a register ring of P slices
-// (non-temporal; four slices at 256 head rows, where the accumulators fill the
-// AGPRs), while the head rows' 64-k slice of each k-step is staged by LDS-DMA
-// in a 4-stage ring (one barrier per k-step) that all four waves read.
-// In the LDS-ring kernel above every wave re-reads all head rows from LDS for
-// its 32 vocabulary rows; here each head-row fragment serves two MFMAs and the
-// vocabulary rows never touch LDS.  Per slice a wave runs 2 TI MFMAs with W as
+// (128 HV); wave w owns the tile's 32-row groups TJ w .., whose 1 KiB operands
+// stream straight from the copy into a register ring of P slices
+// (non-temporal), while the head rows' 64-k slice of each k-step is staged by
+// LDS-DMA in a 4-stage ring (one barrier per k-step) that all waves read.  The
+// vocabulary rows never touch LDS.  Per slice a wave runs TJ TI MFMAs with W as
 // the A operand; at the end of a tile the lanes' entries are reduced
 // (tile_stat), merged across the waves through LDS into the per-row running
 // statistics, and the workgroups' partials merged as in the other kernels.
 // The ring's issue order and wait counts are those of the register-direct GEMM
-// (stages of one 64-k step: four slices per stage, two DMA loads per slice).
-template <int TI, bool LG>
-__global__ void __launch_bounds__(256, 1) head_wd_kernel(HeadArgs a) {
+// (stages of one 64-k step: four slices per stage).
+//
+// Up to 128 head rows (HV = 1) four waves of two groups each: bound by the W
+// stream.  Up to 256 (HV = 2) eight waves of one group each: near the ridge, so
+// what counts is W in flight (64 KiB a CU) and a second wave per SIMD to run
+// MFMAs while one waits.  At 256 rows x 126464 x 4096: 269 us (0.99 PFLOP/s, 3.9
+// TB/s); four waves of two groups, whose 256 accumulators a lane left room for a
+// four-slice ring, 298; eight waves of two groups x 128 rows, each W operand
+// loaded twice, 308 (40% more L2 misses); touching W's lines two stages ahead
+// to bring them into L2 made both slower (the stages overflow the XCD's 4 MiB).
+template <int HV, bool LG>
+__global__ void __launch_bounds__(256 * HV, 1) head_wd_kernel(HeadArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  // a 4-slice weight ring at 256 head rows, where the accumulators fill the AGPRs
-  constexpr int NW = 4, NT = 256, TJ = 2, AS = 4, P = TI == 8 ? 4 : 8, U = 4, BM = 32 * TI, R2 = P / U;
+  constexpr int NW = 4 * HV, NT = 64 * NW, TJ = 2 / HV, TI = 4 * HV, AS = 4, P = 8, U = 4, BM = 32 * TI, R2 = P / U;
   constexpr int STAGE = BM * 128;   // head rows x 64 k
   constexpr int IA = BM / 8 / NW;   // DMA loads per wave per stage
   constexpr int IU = IA / U;        // ... per slice
@@ -437,7 +448,7 @@ __global__ void __launch_bounds__(256, 1) head_wd_kernel(HeadArgs a) {
   const int my_tiles = blockIdx.x < ntiles ? (ntiles - 1 - blockIdx.x) / G + 1 : 0;
   const int units = my_tiles * nk;  // stages: (tile, 64-k step)
 
-  // head-row DMA: instruction q of wave w fills rows 8 (4 q + w) .. +7; lane l
+  // head-row DMA: instruction q of wave w fills rows 8 (NW q + w) .. +7; lane l
   // writes row + l/8, slot l%8 holding chunk (l%8) ^ ((row >> 1) & 7); rows
   // past R repeat the last row (never used)
   const int dr = lane >> 3, dc = (lane & 7) ^ (((wave & 1) << 2) | (dr >> 1));
@@ -445,7 +456,7 @@ __global__ void __launch_bounds__(256, 1) head_wd_kernel(HeadArgs a) {
   uint32_t voh[IA];
 #pragma unroll
   for (int q = 0; q < IA; ++q) {
-    const int row = min(8 * (4 * q + wave) + dr, a.R - 1);
+    const int row = min(8 * (NW * q + wave) + dr, a.R - 1);
     voh[q] = (uint32_t)(((size_t)row * a.d + dc * 8) * 2);
   }
   // stage u's LDS slot and head-row k offset (past the end: the last stage
@@ -458,15 +469,15 @@ __global__ void __launch_bounds__(256, 1) head_wd_kernel(HeadArgs a) {
     return (uint32_t)(((size_t)(blockIdx.x + i * G) * nk + (u - i * nk)) * (HEAD_TILE / 32) * 4 * 1024);
   };
   auto issue_a = [&](int slot, int soff, int q) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rh, (lds_ptr_t)(lds + slot * STAGE + 8 * (4 * q + wave) * 128), 16,
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rh, (lds_ptr_t)(lds + slot * STAGE + 8 * (NW * q + wave) * 128), 16,
                                              voh[q], soff, 0, 0);
   };
   const uint32_t wbytes = (uint32_t)head_bf16_packed_bytes_dev(a.V, a.d);
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)a.W, 0, wbytes, 0x00020000);
   typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
   u32x4_t wbuf[P][TJ];
-  const uint32_t wlane = (uint32_t)(2 * wave * 4 * 1024 + lane * 16);
-  // operand j (group 2 wave + j of the tile) of slice sl of the stage whose run starts at run
+  const uint32_t wlane = (uint32_t)(TJ * wave * 4 * 1024 + lane * 16);
+  // operand j (group TJ wave + j of the tile) of slice sl of the stage whose run starts at run
   auto load_w = [&](uint32_t run, int sl, int slot, int j) {
     wbuf[slot][j] = __builtin_amdgcn_raw_buffer_load_b128(rw, run + wlane + (uint32_t)((j * 4 + sl) * 1024), 0,
                                                           CPOL_NT);
@@ -549,13 +560,16 @@ __global__ void __launch_bounds__(256, 1) head_wd_kernel(HeadArgs a) {
     }
     __builtin_amdgcn_sched_barrier(0);
     // end of a vocabulary tile: lane holds head row 32 ii + lrow, entries
-    // v0 + 8 (r / 4) + 4 lhalf + r % 4 of group 2 wave + j
+    // v0 + 8 (r / 4) + 4 lhalf + r % 4 of group TJ wave + j
     const int t = blockIdx.x + ti * G;
 #pragma unroll
     for (int ii = 0; ii < TI; ++ii) {
-      Stat st = tile_stat<LG>(a, acc[0][ii], 32 * ii + lrow, t * HEAD_TILE + (2 * wave) * 32, lhalf);
-      st = merge(st, tile_stat<LG>(a, acc[1][ii], 32 * ii + lrow, t * HEAD_TILE + (2 * wave + 1) * 32, lhalf));
-      if (lhalf == 0) wst[wave][32 * ii + lrow] = st;
+      const int row = 32 * ii + lrow;
+      Stat st = tile_stat<LG>(a, acc[0][ii], row, t * HEAD_TILE + (TJ * wave) * 32, lhalf);
+#pragma unroll
+      for (int j = 1; j < TJ; ++j)
+        st = merge(st, tile_stat<LG>(a, acc[j][ii], row, t * HEAD_TILE + (TJ * wave + j) * 32, lhalf));
+      if (lhalf == 0) wst[wave][row] = st;
       __builtin_amdgcn_sched_barrier(0);  // one row block at a time (register pressure)
     }
 #pragma unroll
@@ -685,25 +699,25 @@ void launch_head_bf16(const HeadArgs& a, hipStream_t s) {
     const int ntiles = (a.V + HEAD_TILE - 1) / HEAD_TILE, cus = std::min(device_cu_count(), MAX_WG);
     const int per = (ntiles + cus - 1) / cus, grid = (ntiles + per - 1) / per;
     // the variant that also stores the logits (a debug buffer) is its own kernel
-    auto go1 = [&](auto tic, auto lgc) {
-      constexpr int TI = decltype(tic)::value;
+    auto go1 = [&](auto hvc, auto lgc) {
+      constexpr int HV = decltype(hvc)::value;
       constexpr bool LG = decltype(lgc)::value;
-      constexpr size_t lds = (size_t)4 * TI * 32 * 128;
-      static const hipError_t attr = hipFuncSetAttribute((const void*)head_wd_kernel<TI, LG>,
+      constexpr size_t lds = (size_t)4 * HV * 128 * 128;
+      static const hipError_t attr = hipFuncSetAttribute((const void*)head_wd_kernel<HV, LG>,
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       hip_check(attr, "hipFuncSetAttribute(head_wd)");
-      hipLaunchKernelGGL((head_wd_kernel<TI, LG>), dim3(grid), dim3(256), lds, s, a);
+      hipLaunchKernelGGL((head_wd_kernel<HV, LG>), dim3(grid), dim3(256 * HV), lds, s, a);
     };
-    auto go = [&](auto tic) {
+    auto go = [&](auto hvc) {
       if (a.logits)
-        go1(tic, std::true_type{});
+        go1(hvc, std::true_type{});
       else
-        go1(tic, std::false_type{});
+        go1(hvc, std::false_type{});
     };
     if (rg <= 4)
-      go(std::integral_constant<int, 4>{});
+      go(std::integral_constant<int, 1>{});
     else
-      go(std::integral_constant<int, 8>{});
+      go(std::integral_constant<int, 2>{});
   } else if (rg <= 1) HeadCfg<1, 256, 8, 4>::launch(a, s);
   else HeadCfg<2, 256, 8, 3>::launch(a, s);
   DLLM_LAUNCH_CHECK("head_bf16");

@@ -71,3 +71,29 @@ def test_folded_residual_sums_equal_the_reduction(gpu_lib, rows):
     _, _, calls = model.head_noalloc(h, 1, rows, 0, rows, logits=True)
     assert torch.equal(fused.view(torch.int32), calls.view(torch.int32))
     assert torch.equal(kv, kv2)
+
+
+@pytest.mark.parametrize("rows", [33, 64, 65, 128, 129, 224, 256])
+@pytest.mark.parametrize("V,mask", [(1000, 999), (515, 512), (257, 0)])
+def test_head_rows_and_vocabulary_edges(gpu_lib, monkeypatch, rows, V, mask):
+    """The head kernels' row counts and vocabulary remainders, with and without the logits buffer: the mask id first,
+    in the last partial group or alone past a whole tile; confidences against float64 of the kernel's own logits."""
+    d = 256
+    cfg = synth.ModelConfig("head-edge", n_layers=0, d_model=d, n_heads=2, n_kv_heads=2, head_dim=128, d_ff=128,
+                            vocab=V, rope_base=10000.0, dtype="bf16", lm_head_std=5 / math.sqrt(d))
+    w = [t.cuda() for t in synth.make_weights(cfg, "cpu")]
+    c = B.model_cfg(cfg)
+    c.mask_id = mask
+    monkeypatch.setattr(B, "model_cfg", lambda _: c)
+    model = B.Model(cfg, w)
+    h = synth.make_normal((rows, d), 9).cuda()
+    Bn = 4 if rows % 4 == 0 else 1
+    conf, arg, lg = model.head_noalloc(h, Bn, rows // Bn, 0, rows // Bn, logits=True)
+    conf2, arg2, _ = model.head_noalloc(h, Bn, rows // Bn, 0, rows // Bn)
+    assert torch.equal(conf.view(torch.int32), conf2.view(torch.int32)) and torch.equal(arg, arg2)
+    x = lg.view(rows, V).double().cpu().numpy()
+    x[:, mask] = -np.inf
+    p = 1.0 / np.exp(x - x.max(-1, keepdims=True)).sum(-1)
+    # float32 exponentials and sums of up to 1000 terms: a few 2^-24 each
+    np.testing.assert_allclose(conf.view(-1).cpu().numpy(), p, rtol=3e-6)
+    np.testing.assert_array_equal(arg.view(-1).cpu().numpy(), x.argmax(-1))
