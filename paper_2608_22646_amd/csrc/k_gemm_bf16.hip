@@ -15,7 +15,8 @@
 //   RESID  : plain W; the epilogue adds the result to the float32 residual.
 //
 // Tiling: BM x BN x 64 per workgroup of 4 or 8 wavefronts, each wave owning a
-// 64 x 128 or 64 x 96 block of 32x32 MFMA tiles (v_mfma_f32_32x32x16_bf16).
+// 64 x 128 or 64 x 96 block of 32x32 MFMA tiles (v_mfma_f32_32x32x16_bf16); the
+// 256-row tiles run on 16x16x32 (gemm16_kernel).
 // Tiles of A and Bv stream from memory straight into a 2- or 3-stage LDS ring
 // (buffer_load_dwordx4 ... lds, no staging registers), with one barrier per
 // k-step.  LDS rows are 128 bytes (64 bf16); the 16-byte chunk c of row r is
@@ -29,6 +30,8 @@
 // Split-K (RESID only): grid.z slices of K write float32 partial tiles; a second
 // kernel adds them to the residual in slice order (deterministic, no atomics).
 #include "kernels.h"
+
+#include <type_traits>
 
 namespace dllm {
 
@@ -92,10 +95,6 @@ struct Tile {
 };
 // 128 x 256, 4 waves of 64 x 128, three stages (small M: more tiles to spread over 256 CUs)
 using TileS = Tile<128, 256, 2, 2, 3>;
-// 256 x 256, 8 waves of 64 x 128 (two per SIMD), two stages (large M: fewer bytes per flop)
-using TileL = Tile<256, 256, 4, 2, 2>;
-// 256 x 192, 8 waves of 64 x 96: at M = 512, N = 24576 it makes exactly 256 tiles
-using TileM = Tile<256, 192, 4, 2, 2>;
 // 128 x 192, 4 waves of 64 x 96, three stages
 using TileSM = Tile<128, 192, 2, 2, 3>;
 // the same on 8 waves in two k-groups
@@ -682,6 +681,282 @@ __global__ void __launch_bounds__(TL::NTH, 1) gemm_bf16_kernel(GemmArgs g) {
     epilogue_staged<TL, EPI>(g, lds, wave, lane, o.x, o.y, acc);
   else
     epilogue_resid<TL>(g, wave, lane, o.x, o.y, acc);
+#endif
+}
+
+// Stage one token row's values of a 32-row virtual block (tile block jb, virtual
+// row vb): a 16 x 16 x 32 MFMA with W as its A operand leaves virtual rows
+// 4 q4 .. + 3 in lo and 16 + 4 q4 .. + 3 in hi, the two operands of an output
+// side by side in one lane.
+template <int BM, int BN, int EPI>
+__device__ __forceinline__ void stage_pair(const GemmArgs& g, char* lds, int ml, int pos, int jb, int vb, int q4,
+                                           const f32x4_t& lo, const f32x4_t& hi, bool& v_over) {
+  using St = StageGeo<BM, BN>;
+  constexpr int HD = 128, HALF = 64;
+  const int nq = g.Hq * HD, nkv = g.Hkv * HD;
+  char* blk = lds + jb * St::BLK;
+  if (EPI == EPI_SWIGLU) {  // gate, up
+    float u[4];
+    // silu with the hardware exp2 and reciprocal: the result is rounded to bf16
+#pragma unroll
+    for (int e = 0; e < 4; ++e) u[e] = __fdividef(lo[e], 1.0f + __expf(-lo[e])) * hi[e];
+    *reinterpret_cast<uint2*>(lds + ml * St::SW_ROW + (16 * jb + 4 * q4) * 2) =
+        make_uint2(pack_bf16x2(u[0], u[1]), pack_bf16x2(u[2], u[3]));
+  } else if (vb < nq + nkv) {  // q or k: dimension d and d + 64 of one head
+    const int rel = vb < nq ? vb : vb - nq, d = 16 * ((rel % HD) >> 5) + 4 * q4;
+    const f32x4_t c4 = *reinterpret_cast<const f32x4_t*>(g.cosb + (size_t)pos * HALF + d);
+    const f32x4_t s4 = *reinterpret_cast<const f32x4_t*>(g.sinb + (size_t)pos * HALF + d);
+    float a[4], b[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      a[e] = lo[e] * c4[e] - hi[e] * s4[e];
+      b[e] = hi[e] * c4[e] + lo[e] * s4[e];
+    }
+    *reinterpret_cast<uint2*>(blk + ml * 64 + 8 * q4) = make_uint2(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]));
+    *reinterpret_cast<uint2*>(blk + ml * 64 + 32 + 8 * q4) =
+        make_uint2(pack_bf16x2(b[0], b[1]), pack_bf16x2(b[2], b[3]));
+  } else {  // v, staged as v^T
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      *reinterpret_cast<f16_t*>(blk + (4 * q4 + e) * St::VROW + ml * 2) = v_half(lo[e], v_over);
+      *reinterpret_cast<f16_t*>(blk + (16 + 4 * q4 + e) * St::VROW + ml * 2) = v_half(hi[e], v_over);
+    }
+  }
+}
+
+// ---- 256-row tiles on 16 x 16 x 32 MFMAs ------------------------------------
+//
+// At a few thousand rows every SIMD's matrix core is wanted all the time and the
+// card lowers the clock to stay in its power budget, so the energy of an
+// instruction counts: an MFMA-only loop on random operands ran at 2.07 PFLOP/s
+// with 16 x 16 x 32 and at 1.82 with 32 x 32 x 16 (per flop it reads and writes
+// each accumulator half as often).  The rest of the difference to the 32 x 32
+// kernel above is when the LDS-DMA is issued: eight waves issue their own,
+// between MFMAs, instead of half of them in one burst; and the activations have
+// three slots of 64 k and the weights two (all 160 KiB of LDS at 256 x 256), so
+// that a k-step's barrier waits only for what was requested a slice and a half
+// before.
+// W is the MFMA A operand, so a lane ends with four neighbouring output columns
+// of one token row: the SwiGLU and rotate-half operands meet without an exchange
+// and the residual moves in 16-byte pieces.
+//
+// 8192 rows of LLaDA-8B (32 x 32 kernel; this with two slots for both operands;
+// now): gate/up 1349, 1214, 1187 us (1.39 PFLOP/s; a plain library product of that
+// shape 1092), q/k/v 716, 657, 639, output and down projections 465, 430, 419 on
+// average.  Dream-7B gate/up at 8448 rows 1944, 1752, 1693.  256 x 192, gate/up: 512
+// rows 107, 101, 97; 300 rows 97, 92, 88.  Matrix cores busy 69% of the cycles with two
+// slots, at 1.84 GHz; LDS moves 256 KiB a k-step, near its rate.
+// Four waves of 128 x 128 (a quarter less LDS traffic, one wave per SIMD): gate/up
+// 1186, the projections 415, q/k/v 656; Dream-7B 1721, 526 against 533, 288 against 270.
+// 16 x 16 x 32 in the register-direct kernel below changed nothing: its loads bound it.
+template <int BM_, int BN_, int WAVES_M, int WAVES_N>
+struct Tile16 {
+  static constexpr int BM = BM_, BN = BN_, NWN = WAVES_N;
+  static constexpr int NW = WAVES_M * WAVES_N, NTH = 64 * NW;
+  static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
+  static constexpr int TI = WM / 16, TJ = WN / 16;         // 16 x 16 blocks per wave
+  static constexpr int IA = BM / 8 / NW, IB = BN / 8 / NW;  // LDS-DMA instructions per wave per k-step
+  static_assert(WM % 16 == 0 && WN % 32 == 0, "whole output blocks, whole 32-row epilogue groups");
+  static_assert(IA * NW * 8 == BM && IB * NW * 8 == BN, "tile rows must split evenly over the DMA loads");
+  static_assert(NW % 2 == 0, "the DMA swizzle assumes an even wave count");
+};
+// 256 x 256, 8 waves of 64 x 128 (two per SIMD; large M: fewer bytes per flop)
+using TileL = Tile16<256, 256, 4, 2>;
+// 256 x 192, 8 waves of 64 x 96: at M = 512, N = 24576 it makes exactly 256 tiles
+using TileM = Tile16<256, 192, 4, 2>;
+
+template <class TL, int EPI>
+constexpr size_t lds_bytes16() {
+  using St = StageGeo<TL::BM, TL::BN>;
+  const size_t ring = (size_t)(3 * TL::BM + 2 * TL::BN) * 128;
+  const size_t st = EPI == EPI_SWIGLU ? St::SW_BYTES : EPI == EPI_QKV_ROPE ? St::QKV_BYTES : 0;
+  return ring > st ? ring : st;
+}
+
+template <class TL, int EPI>
+__global__ void __launch_bounds__(TL::NTH, 1) gemm16_kernel(GemmArgs g) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  constexpr int BM = TL::BM, BN = TL::BN, NW = TL::NW, TI = TL::TI, TJ = TL::TJ;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / TL::NWN, wn = wave % TL::NWN;
+  const int tiles = ((g.M + BM - 1) / BM) * (g.N / BN);
+  // XCD-contiguous (split, tile) order, K slices and the DMA's lane layout as in gemm_bf16_kernel
+  const int T = tiles * (int)gridDim.z, bi = blockIdx.x + tiles * blockIdx.z, x = bi & 7;
+  const int li = x * (T >> 3) + min(x, T & 7) + (bi >> 3);
+  const int lin = li % tiles, zs = li / tiles;
+  const int2 o = tile_origin<TL>(g, lin);
+  const int m0 = o.x, n0 = o.y;
+  const int ks_total = g.K / BK;
+  const int kt0 = (int)((long)zs * ks_total / gridDim.z);
+  const int nk = (int)((long)(zs + 1) * ks_total / gridDim.z) - kt0;
+
+  const int lr = lane >> 3, lc = (lane & 7) ^ (((wave & 1) << 2) | (lr >> 1));
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)g.A, 0, 0x7fffffff, 0x00020000);
+  uint32_t voa[TL::IA], vob[TL::IB];
+#pragma unroll
+  for (int i = 0; i < TL::IA; ++i) {
+    const int row = min(m0 + 8 * (NW * i + wave) + lr, g.M - 1);
+    voa[i] = (uint32_t)(((size_t)row * g.K + lc * 8) * 2);
+  }
+  const bf16_t* wsrc[3] = {g.W0, g.W1, g.W2};
+  __amdgpu_buffer_rsrc_t rbs[TL::IB];
+#pragma unroll
+  for (int i = 0; i < TL::IB; ++i) {
+    const int2 first = vrow<EPI>(g, n0 + 8 * (NW * i + wave));  // wave-uniform
+    rbs[i] = __builtin_amdgcn_make_buffer_rsrc((void*)wsrc[first.x], 0, 0x7fffffff, 0x00020000);
+    vob[i] = (uint32_t)(((size_t)(first.y + lr) * g.K + lc * 8) * 2);
+  }
+  // DMA instruction d of k-step kt into a slot: weights, activations
+  char* const ldsb = lds + 3 * BM * 128;
+  auto issue_b = [&](int kt, int slot, int d) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rbs[d], (lds_ptr_t)(ldsb + slot * (BN * 128) + 8 * (NW * d + wave) * 128), 16,
+                                             vob[d], (kt0 + kt) * BK * 2, 0, 0);
+  };
+  auto issue_a = [&](int kt, int slot, int d) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr_t)(lds + slot * (BM * 128) + 8 * (NW * d + wave) * 128), 16,
+                                             voa[d], (kt0 + kt) * BK * 2, 0, 0);
+  };
+
+  f32x4_t acc[TJ][TI];
+#pragma unroll
+  for (int j = 0; j < TJ; ++j)
+#pragma unroll
+    for (int i = 0; i < TI; ++i) acc[j][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  const int l16 = lane & 15, q4 = lane >> 4;
+  bf16x8_t af[2][TI], wf[2][TJ];
+  constexpr int NF = TI + TJ, NM = TI * TJ;
+  // fragment f (weight rows first) of 32-k slice ks
+  auto frag = [&](int as, int bs, int ks, int f) {
+    if (f < TJ)
+      wf[ks][f] = *reinterpret_cast<const bf16x8_t*>(ldsb + bs * (BN * 128) + swz(wn * TL::WN + f * 16 + l16, ks * 4 + q4));
+    else
+      af[ks][f - TJ] =
+          *reinterpret_cast<const bf16x8_t*>(lds + as * (BM * 128) + swz(wm * TL::WM + (f - TJ) * 16 + l16, ks * 4 + q4));
+  };
+  // The MFMAs of slice ks in NC pinned groups, the next slice's fragment reads
+  // in the first three quarters of them, with the activations' DMA spread over
+  // slice 0 and the weights' over the first half of slice 1.  (Left to the
+  // scheduler, all reads follow all DMA: it cannot tell their slots apart.)
+  constexpr int NC = NM % 16 == 0 ? 16 : 8;
+  static_assert(NM % NC == 0, "equal groups");
+  auto slice = [&](int ks, int fas, int fbs, int fks, auto read, auto dma, int dkt, int slot) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      if (decltype(read)::value) {
+        const int f0 = min(NF, (c * NF * 4 + NC * 3 - 1) / (NC * 3)), f1 = min(NF, ((c + 1) * NF * 4 + NC * 3 - 1) / (NC * 3));
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+          if (f >= f0 && f < f1) frag(fas, fbs, fks, f);
+      }
+#pragma unroll
+      for (int d = 0; d < (ks ? TL::IB : TL::IA); ++d) {
+        if (!decltype(dma)::value) continue;
+        if (ks == 0 && c == d * NC / TL::IA) issue_a(dkt, slot, d);
+        if (ks == 1 && c == d * NC / (2 * TL::IB)) issue_b(dkt, slot, d);
+      }
+#pragma unroll
+      for (int m = c * (NM / NC); m < (c + 1) * (NM / NC); ++m) {
+        const int i = m / TJ, j = m % TJ;
+        acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ks][j], af[ks][i], acc[j][i], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  const std::true_type yes;
+  const std::false_type no;
+
+  for (int t = 0; t < 2 && t < nk; ++t) {
+#pragma unroll
+    for (int d = 0; d < TL::IB; ++d) issue_b(t, t, d);
+#pragma unroll
+    for (int d = 0; d < TL::IA; ++d) issue_a(t, t, d);
+  }
+  if (nk > 1)
+    wait_vm_lds<TL::IA + TL::IB>();
+  else
+    wait_vm_lds<0>();
+  barrier_nofence();
+#pragma unroll
+  for (int f = 0; f < NF; ++f) frag(0, 0, 0, f);
+  int as = 0;  // kt % 3
+  // k-step kt.  Slice 0 requests the activations of kt + 2 (into the slot kt - 1
+  // left), slice 1, after the barrier that ends the reads of kt, its weights.  At
+  // that barrier the activations of kt + 2 alone may still be in flight.
+  auto step = [&](int kt, auto dma, auto next) {
+    const int bs = kt & 1, as1 = as == 2 ? 0 : as + 1, as2 = as1 == 2 ? 0 : as1 + 1;
+    __builtin_amdgcn_sched_barrier(0);
+    slice(0, as, bs, 1, yes, dma, kt + 2, as2);
+    if (decltype(next)::value) {
+      wait_vm_lds<decltype(dma)::value ? TL::IA : 0>();
+      barrier_nofence();
+      __builtin_amdgcn_sched_barrier(0);
+      slice(1, as1, bs ^ 1, 0, yes, dma, kt + 2, bs);
+    } else {
+      slice(1, as1, bs ^ 1, 0, no, no, 0, 0);
+    }
+    as = as1;
+  };
+  int kt = 0;
+  for (; kt + 2 < nk; ++kt) step(kt, yes, yes);
+  if (kt + 1 < nk) step(kt++, no, yes);
+  step(kt, no, no);
+
+  // Lane l of block (j, i) holds token row 16 i + l % 16 and, in register e,
+  // virtual weight row 16 j + 4 (l / 16) + e of the wave's tile.
+  if constexpr (EPI == EPI_RESID) {
+    const int n = n0 + wn * TL::WN + 4 * q4;
+    const bool part = gridDim.z > 1;
+    float* dst = part ? g.splitk_buf + (size_t)zs * g.M * g.N : g.resid;
+    constexpr int RB = 2;
+#pragma unroll
+    for (int i0 = 0; i0 < TI; i0 += RB) {
+      f32x4_t h[RB][TJ];
+      if (!part) {
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+          const int m = min(m0 + wm * TL::WM + (i0 + i) * 16 + l16, g.M - 1);
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) h[i][j] = *reinterpret_cast<const f32x4_t*>(dst + (size_t)m * g.N + n + j * 16);
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) h[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < RB; ++i) {
+        const int m = m0 + wm * TL::WM + (i0 + i) * 16 + l16;
+        if (m >= g.M) continue;
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+          *reinterpret_cast<f32x4_t*>(dst + (size_t)m * g.N + n + j * 16) = h[i][j] + acc[j][i0 + i];
+      }
+    }
+  } else {
+    const float inv_l = 1.0f / (float)g.Lq;
+    bool v_over = false;
+    wait_vm_lds<0>();
+    barrier_nofence();  // every wave is done reading the ring
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      const int ml = wm * TL::WM + 16 * i + l16, m = min(m0 + ml, g.M - 1);  // rows past M are staged, never stored
+      int pos = 0;
+      if (EPI == EPI_QKV_ROPE) pos = g.pos0 + seq_pos(m, g.Lq, inv_l).y;
+#pragma unroll
+      for (int jj = 0; jj < TJ / 2; ++jj) {
+        const int jb = wn * (TL::WN / 32) + jj;
+        stage_pair<BM, BN, EPI>(g, lds, ml, pos, jb, n0 + 32 * jb, q4, acc[2 * jj][i], acc[2 * jj + 1][i], v_over);
+      }
+    }
+    if (EPI == EPI_QKV_ROPE && v_over && g.err) atomicOr(g.err, (int)ERR_V_RANGE);
+    __builtin_amdgcn_s_waitcnt((15) | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0)
+    barrier_nofence();
+    staged_store<BM, BN, TL::NTH, EPI>(g, lds, m0, n0);
+  }
 #endif
 }
 
@@ -1566,6 +1841,16 @@ void launch_tile(const GemmArgs& g, int split, hipStream_t s) {
   hipLaunchKernelGGL((gemm_bf16_kernel<TL, EPI, PB>), dim3(tiles, 1, split), dim3(TL::NTH), lds, s, g);
 }
 
+template <class TL, int EPI>
+void launch_tile16(const GemmArgs& g, int split, hipStream_t s) {
+  const int tiles = ((g.M + TL::BM - 1) / TL::BM) * (g.N / TL::BN);
+  const size_t lds = lds_bytes16<TL, EPI>();
+  static const hipError_t attr = hipFuncSetAttribute((const void*)gemm16_kernel<TL, EPI>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hip_check(attr, "hipFuncSetAttribute(gemm16)");
+  hipLaunchKernelGGL((gemm16_kernel<TL, EPI>), dim3(tiles, 1, split), dim3(TL::NTH), lds, s, g);
+}
+
 template <int EPI>
 void launch_epi(const GemmArgs& g, const Plan& p, hipStream_t s) {
   if (p.bm == 64 && g.Wp)
@@ -1575,9 +1860,9 @@ void launch_epi(const GemmArgs& g, const Plan& p, hipStream_t s) {
   else if (p.bm == 128 && p.bn == 128)
     launch_tile<TileQ, EPI>(g, p.split, s);
   else if (p.bm == 256 && p.bn == 256)
-    launch_tile<TileL, EPI>(g, p.split, s);
+    launch_tile16<TileL, EPI>(g, p.split, s);
   else if (p.bm == 256)
-    launch_tile<TileM, EPI>(g, p.split, s);
+    launch_tile16<TileM, EPI>(g, p.split, s);
   else if (p.bn == 256)
     launch_tile<TileS, EPI>(g, p.split, s);
   else
