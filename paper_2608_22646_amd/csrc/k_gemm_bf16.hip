@@ -17,7 +17,7 @@
 // Tiling: BM x BN x 64 per workgroup of 4 or 8 wavefronts, each wave owning a
 // 64 x 128 or 64 x 96 block of 32x32 MFMA tiles (v_mfma_f32_32x32x16_bf16); the
 // 256-row tiles run on 16x16x32 (gemm16_kernel).
-// Tiles of A and Bv stream from memory straight into a 2- or 3-stage LDS ring
+// Tiles of A and Bv stream from memory straight into a 3- or 4-stage LDS ring
 // (buffer_load_dwordx4 ... lds, no staging registers), with one barrier per
 // k-step.  LDS rows are 128 bytes (64 bf16); the 16-byte chunk c of row r is
 // stored at slot c ^ ((r >> 1) & 7), so the sixteen rows read by sixteen
@@ -172,8 +172,8 @@ __device__ __forceinline__ void mma_tile(const GemmArgs& g, char* lds, int wave,
   const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)g.A, 0, 0x7fffffff, 0x00020000);
   // In 8-wave tiles only waves 0..3 (one per SIMD) issue the DMA, each for its
   // own rows and those of wave + 4: an LDS-DMA burst stalls the issuing wave,
-  // and the other wave of its SIMD keeps the MFMA pipe busy meanwhile (gate/up
-  // at M = 8192: 1496 -> 1415 us; 1-4% at M = 512).  wave + 4 has the same
+  // and the other wave of its SIMD keeps the MFMA pipe busy meanwhile (1-4% at
+  // M = 512).  wave + 4 has the same
   // parity, so the same chunk swizzle.
   constexpr int HW = NW == 8 ? 2 : 1;  // waves whose DMA one issuing wave covers
   const bool issuer = HW == 1 || wave < NW / 2;
@@ -1771,8 +1771,10 @@ struct Plan {
 // Pick the tile and a K split (any count up to 8, or 16 for launches of at most
 // 128 rows; the k-steps are spread as evenly as they divide), by a time model:
 // rounds of workgroups over the 256 compute units x k-steps per workgroup x
-// the tile's k-step time (measured on random bf16 data at M = 512: larger
-// tiles move fewer LDS bytes per flop and run two waves per SIMD), plus, for
+// the tile's k-step time (measured on random bf16 data at M = 512 with every
+// tile on 32 x 32 x 16 MFMAs: larger tiles move fewer LDS bytes per flop and run
+// two waves per SIMD; the 256-row tiles take about a tenth less since they
+// run on 16 x 16 x 32, which no width has been moved over the line for), plus, for
 // the residual GEMMs, the memory time of the float32 partials (written here,
 // read back by the reduction) or of the residual's read-modify-write, at the
 // ~8 TB/s they move at (measured: much of it stays in the last-level cache).
