@@ -399,14 +399,17 @@ __global__ void __launch_bounds__(HD == 64 ? 512 : 256) attn_f32_kernel(const fl
     }
     mt = fmax(mt, __shfl_xor(mt, 16, 64));
     mt = fmax(mt, __shfl_xor(mt, 32, 64));
-    const double mn = fmax(m, mt);
-    if (mn == -INFINITY) continue;  // every score so far is -inf: nothing to add
-    const double alpha = exp(m - mn);
+    // While every score of a query is -inf or NaN (which fmax drops) its maximum
+    // is -inf: then scores are taken against 0, so that -inf adds nothing and NaN
+    // stays NaN.  No branch: queries would differ in it, and the MFMAs below read
+    // V of every lane.
+    const double mn = fmax(m, mt), ref = mn == -INFINITY ? 0.0 : mn;
+    const double alpha = exp(m - ref);
     m = mn;
     l *= alpha;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      sc[r] = exp(sc[r] - mn);
+      sc[r] = exp(sc[r] - ref);
       l += sc[r];
     }
 #pragma unroll
@@ -432,7 +435,7 @@ __global__ void __launch_bounds__(HD == 64 ? 512 : 256) attn_f32_kernel(const fl
 #pragma unroll
   for (int w = 0; w < NW; ++w) mm = fmax(mm, mx[w][col]);
 #pragma unroll
-  for (int w = 0; w < NW; ++w) {  // a wave that saw no key (m = -inf) adds nothing
+  for (int w = 0; w < NW; ++w) {  // a wave that saw no key (m = -inf, sums zero) adds nothing; a NaN sum stays
     a[w] = mx[w][col] == -INFINITY ? 0.0 : exp(mx[w][col] - mm);
     ll += lx[w][col] * a[w];
   }

@@ -73,3 +73,65 @@ def test_scores_of_minus_infinity_drop_out(gpu_lib):
     p = np.exp(sc - sc.max(-1, keepdims=True))
     ref = ((p / p.sum(-1, keepdims=True))[:, None] * vv).sum(-1)
     np.testing.assert_allclose(got, ref, rtol=1e-6, atol=1e-6)
+
+
+def windowed(cfg, w, x, row0, rows):
+    """Layer 0's attention half on a window of the sequence x over a random cache: (q, K, V^T, attention output)
+    in float64, and a function that runs the half again."""
+    model = B.Model(cfg, [t.cuda() for t in w])
+    L, H, hd = x.shape[1], cfg.n_heads, cfg.head_dim
+    ws, kv, lay = model.workspace(1, L, rows), model.kv_cache(1, L), model.layout(1, L, rows)
+    n = cfg.n_kv_heads * L * hd
+    K = kv[:4 * n].view(torch.float32).view(cfg.n_kv_heads, L, hd)
+    V = kv[4 * n:8 * n].view(torch.float32).view(cfg.n_kv_heads, hd, L)
+    kv.zero_()
+    K.copy_(synth.make_normal(K.shape, 7))
+    V.copy_(synth.make_normal(V.shape, 8))
+    model.embed_rows(x.cuda(), row0, rows, ws)
+
+    def run():
+        model.layer_kv(0, 0, 1, L, row0, rows, kv, ws)
+        q = ws[lay.q:lay.q + 4 * H * rows * hd].view(torch.float32).view(H, rows, hd)
+        out = ws[lay.attn:lay.attn + 4 * rows * H * hd].view(torch.float32).view(rows, H, hd).transpose(0, 1)
+        return [t.double().cpu().numpy() for t in (q, K, V, out)]
+    return K, run
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("first", [0, 48, 96])
+def test_nan_keys_reach_every_query(gpu_lib, hd, first):
+    """A whole 16-key tile of NaN keys, also where it is the first its wave sees."""
+    cfg = config(256, 4, 2, hd, 64, 64)
+    K, run = windowed(cfg, synth.make_weights(cfg, "cpu"), synth.make_ints((1, 150), 3, 0, cfg.vocab), 120, 20)
+    assert np.isfinite(run()[3]).all()
+    K[:, first:first + 16] = math.nan
+    assert np.isnan(run()[3]).all()
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_queries_without_a_score_leave_the_others_alone(gpu_lib, hd):
+    """Some queries of a 16-query tile are NaN (their projection overflows float32), so none of their scores counts;
+    the others' results are the float64 ones."""
+    cfg = config(256, 4, 2, hd, 64, 64)
+    w = synth.make_weights(cfg, "cpu")
+    L, row0, rows, bad = 150, 110, 32, 5
+    w[0][:, 3] = 0.0
+    w[0][bad, 3] = 3.0  # column 3 of h, and with it a q pair of every head, is that token's alone
+    for h in range(cfg.n_heads):
+        for j in (7, 7 + hd // 2):
+            w[2][h * hd + j] = 0.0
+            w[2][h * hd + j, 3] = 3e38
+    x = synth.make_ints((1, L), 3, bad + 1, cfg.vocab)
+    at = [1, 2, 9, 16, 31]
+    x[0, [row0 + i for i in at]] = bad
+    _, run = windowed(cfg, w, x, row0, rows)
+    q, K, V, out = run()
+    good = np.setdiff1d(np.arange(rows), at)
+    assert np.isnan(out[:, at]).all()
+    rep = cfg.n_heads // cfg.n_kv_heads
+    for h in range(cfg.n_heads):
+        sc = q[h, good] @ K[h // rep].T / math.sqrt(hd)
+        p = np.exp(sc - sc.max(-1, keepdims=True))
+        ref = (p / p.sum(-1, keepdims=True)) @ V[h // rep].T
+        # float64 sums on both sides: what differs is one float32 rounding of values of size ~1
+        np.testing.assert_allclose(out[h, good], ref, rtol=1e-6, atol=1e-6)
