@@ -167,9 +167,12 @@ __device__ __forceinline__ void mma_tile(const GemmArgs& g, char* lds, int wave,
   // logical 16-byte chunk (l%8) ^ ((row >> 1) & 7); with NW even, row >> 1
   // = 4 (w & 1) + (l/8) / 2 modulo 8, the same for every i.
   // Row offsets are fixed across k; the k advance goes in the scalar offset.
-  // A rows past M are clamped to M-1 (their results are never stored).
+  // A rows past M are clamped to M-1 (their results are never stored).  Buffer
+  // offsets are 32 bits and end at 2 GiB, which A may pass: its descriptor starts
+  // at the tile's first row.
   const int lr = lane >> 3, lc = (lane & 7) ^ (((wave & 1) << 2) | (lr >> 1));
-  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)g.A, 0, 0x7fffffff, 0x00020000);
+  const __amdgpu_buffer_rsrc_t ra =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(g.A + (size_t)m0 * g.K), 0, 0x7fffffff, 0x00020000);
   // In 8-wave tiles only waves 0..3 (one per SIMD) issue the DMA, each for its
   // own rows and those of wave + 4: an LDS-DMA burst stalls the issuing wave,
   // and the other wave of its SIMD keeps the MFMA pipe busy meanwhile (1-4% at
@@ -183,7 +186,7 @@ __device__ __forceinline__ void mma_tile(const GemmArgs& g, char* lds, int wave,
 #pragma unroll
     for (int i = 0; i < TL::IA; ++i) {
       const int wv = wave + hw * (NW / 2);
-      const int row = min(m0 + 8 * (NW * i + wv) + lr, g.M - 1);
+      const int row = min(8 * (NW * i + wv) + lr, g.M - 1 - m0);
       voa[hw][i] = (uint32_t)(((size_t)row * g.K + kbeg + lc * 8) * 2);
     }
   // Bv rows: each 8-row DMA group lies in one tensor (the tile's q/k/v tensor,
@@ -781,7 +784,7 @@ __global__ void __launch_bounds__(TL::NTH, 1) gemm16_kernel(GemmArgs g) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / TL::NWN, wn = wave % TL::NWN;
   const int tiles = ((g.M + BM - 1) / BM) * (g.N / BN);
-  // XCD-contiguous (split, tile) order, K slices and the DMA's lane layout as in gemm_bf16_kernel
+  // XCD-contiguous (split, tile) order, K slices, the DMA's lane layout and A's descriptor as in gemm_bf16_kernel
   const int T = tiles * (int)gridDim.z, bi = blockIdx.x + tiles * blockIdx.z, x = bi & 7;
   const int li = x * (T >> 3) + min(x, T & 7) + (bi >> 3);
   const int lin = li % tiles, zs = li / tiles;
@@ -792,11 +795,12 @@ __global__ void __launch_bounds__(TL::NTH, 1) gemm16_kernel(GemmArgs g) {
   const int nk = (int)((long)(zs + 1) * ks_total / gridDim.z) - kt0;
 
   const int lr = lane >> 3, lc = (lane & 7) ^ (((wave & 1) << 2) | (lr >> 1));
-  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)g.A, 0, 0x7fffffff, 0x00020000);
+  const __amdgpu_buffer_rsrc_t ra =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(g.A + (size_t)m0 * g.K), 0, 0x7fffffff, 0x00020000);
   uint32_t voa[TL::IA], vob[TL::IB];
 #pragma unroll
   for (int i = 0; i < TL::IA; ++i) {
-    const int row = min(m0 + 8 * (NW * i + wave) + lr, g.M - 1);
+    const int row = min(8 * (NW * i + wave) + lr, g.M - 1 - m0);
     voa[i] = (uint32_t)(((size_t)row * g.K + lc * 8) * 2);
   }
   const bf16_t* wsrc[3] = {g.W0, g.W1, g.W2};

@@ -33,3 +33,19 @@ def test_full_layer(gpu_lib, shape, Bn, L):
     model.embed(synth.make_ints((Bn, L), 5, 0, cfg.vocab).cuda(), ws)
     rows = np.unique(np.concatenate([np.random.default_rng(0).choice(M, 60, replace=False), np.arange(M - 12, M)]))
     check_layer(model, cfg, [t.float().numpy() for t in w], ws, Bn, L, 0, rows=rows)
+
+
+# activations of the down projection beyond 2 GiB, the end of 32-bit buffer offsets (row 56680 at 18944 columns), in
+# one K range (65536 rows) and split over K (65792): every stage of rows around there and in the last sequences
+@pytest.mark.parametrize("L", [4096, 4112])
+def test_activations_beyond_two_gib(gpu_lib, L):
+    cfg = synth.ModelConfig("large-bf16", n_layers=1, d_model=256, n_heads=2, n_kv_heads=2, head_dim=128, d_ff=18944,
+                            vocab=1000, rope_base=10000.0, dtype="bf16", lm_head_std=5 / 16, norm_gain_std=0.1)
+    w = synth.make_weights(cfg, "cpu")
+    model = B.Model(cfg, [t.cuda() for t in w])
+    Bn, edge = 16, 2 ** 31 // (2 * cfg.d_ff)
+    ws = model.workspace(Bn, L, 0)
+    model.embed(synth.make_ints((Bn, L), 5, 0, cfg.vocab).cuda(), ws)
+    rows = np.unique(np.concatenate([np.arange(edge - 6, edge + 6), np.random.default_rng(0).integers(edge, Bn * L, 24),
+                                     np.arange(Bn * L - 6, Bn * L)]))
+    check_layer(model, cfg, [t.float().numpy() for t in w], ws, Bn, L, 0, rows=rows)
