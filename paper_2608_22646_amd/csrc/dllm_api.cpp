@@ -328,6 +328,12 @@ void run_layer_bf16(const dllm_model* m, int layer, int part, int B, int L, void
   const int Lq = rows ? rows->Lq : L, pos0 = rows ? rows->pos0 : 0;
   const int M = B * Lq, d = c.d_model, hd = c.head_dim;
   float* h = at<float>(ws, lay.h);
+  // the GEMMs read a weight tensor through 32-bit buffer offsets that end at 2 GiB
+  for (int w = part == 1 ? 2 : 0; w < (part == 0 ? 2 : 4); ++w) {
+    const GemmArgs g = layer_gemm(m, layer, w);
+    require((size_t)std::max(g.n0, g.n1) * g.K * sizeof(bf16_t) <= 0x7fffffffu, DLLM_EUNSUPPORTED,
+            "bf16 layer weight tensor larger than 2 GiB");
+  }
   PendingResid mid;  // output-projection partials, consumed by the MLP norm
   const bool few = m->packed && gemm_rows_path(M);  // operand-order copies for the few-row GEMMs
   bf16_t* af = few ? at<bf16_t>(ws, lay.af) : nullptr;

@@ -11,6 +11,7 @@ import math
 
 import numpy as np
 import pytest
+import torch
 
 from gpu_stages import check_layer
 from paper_2608_22646_amd import binding as B
@@ -49,3 +50,17 @@ def test_activations_beyond_two_gib(gpu_lib, L):
     rows = np.unique(np.concatenate([np.arange(edge - 6, edge + 6), np.random.default_rng(0).integers(edge, Bn * L, 24),
                                      np.arange(Bn * L - 6, Bn * L)]))
     check_layer(model, cfg, [t.float().numpy() for t in w], ws, Bn, L, 0, rows=rows)
+
+
+def test_weights_beyond_two_gib_are_refused(gpu_lib):
+    """A weight tensor past the end of 32-bit buffer offsets: the layer half that reads it is refused, the other runs."""
+    cfg = synth.ModelConfig("wide-bf16", n_layers=1, d_model=4096, n_heads=2, n_kv_heads=2, head_dim=128, d_ff=262272,
+                            vocab=1000, rope_base=10000.0, dtype="bf16")
+    w = [torch.zeros(shape, dtype=torch.bfloat16, device="cuda") for _, shape, _ in synth.weight_specs(cfg)]
+    model = B.Model(cfg, w)
+    ws = model.workspace(1, 40, 0)
+    model.embed(synth.make_ints((1, 40), 5, 0, cfg.vocab).cuda(), ws)
+    model.layer(0, 0, 1, 40, ws)
+    for part in (1, 2):
+        with pytest.raises(B.DllmError, match="2 GiB"):
+            model.layer(0, part, 1, 40, ws)
