@@ -939,7 +939,8 @@ __global__ void __launch_bounds__(64 * NWS, 1) attn_split_kernel(const bf16_t* _
     for (int j = 0; j < ZB; ++j) {
       if (z0 + j >= NS) break;
       const float mz = __uint_as_float(ml[j][0]);
-      if (mz == -INFINITY) continue;  // a split that saw no key adds nothing
+      // a split that saw no key adds nothing; one whose scores are all NaN has that maximum too, and sums that stay NaN
+      if (mz == -INFINITY && __uint_as_float(ml[j][1]) == 0.f) continue;
       const float mn = fmaxf(m, mz);
       const float ar = m == -INFINITY ? 0.f : exp2_hw(m - mn), az = exp2_hw(mz - mn);
       m = mn;

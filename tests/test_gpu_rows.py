@@ -55,6 +55,26 @@ def test_cached_rows(gpu_lib, shape, Bn, L, row0, rows):
     check_layer_cached(model, cfg, w, ws, kv, Bn, L, row0, rows, 0)
 
 
+# 32 rows and fewer: the keys of a head over four workgroups at these lengths; more: the key-group kernel
+@pytest.mark.parametrize("L,rows", [(515, 20), (544, 32), (515, 50)])
+@pytest.mark.parametrize("first", [0, 128, 256])
+def test_nan_keys_reach_every_query(gpu_lib, L, rows, first):
+    """NaN keys that fill all tiles of one workgroup's share."""
+    cfg, model, _ = model_of(512, 4, 2, 128)
+    kv, ws = model.kv_cache(1, L), model.workspace(1, L, rows)
+    x = synth.make_ints((1, L), 4, 0, cfg.vocab).cuda()
+    model.embed(x, ws)
+    model.layer_kv(0, 2, 1, L, 0, L, kv, ws)
+    out = ws[model.layout(1, L, rows).attn:][:rows * 512 * 2].view(torch.bfloat16)
+    K = kv[:2 * 2 * L * 128].view(torch.bfloat16).view(2, L, 128)
+    for nan in (False, True):
+        if nan:
+            K[:, first:first + 128] = math.nan
+        model.embed_rows(x, L - rows, rows, ws)
+        model.layer_kv(0, 0, 1, L, L - rows, rows, kv, ws)
+        assert (torch.isnan(out) if nan else torch.isfinite(out)).all()
+
+
 @pytest.mark.parametrize("rows", [5, 32, 64])
 def test_folded_residual_sums_equal_the_reduction(gpu_lib, rows):
     cfg, model, _ = model_of(3584, 28, 4, 1408, layers=2)
