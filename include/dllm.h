@@ -397,7 +397,8 @@ int dllm_generate_kv(const dllm_model* model, const dllm_cai_params* params, int
  * 1 = attention, 2 = LM head + reduction, 3 = commit, 4 = norms and
  * embedding (with the residual GEMMs' split-K partials they fold in), 5 =
  * gate/up GEMM (with SwiGLU), 6 = output projection, 7 = down projection.
- * dllm_prof_enable(model, mask) starts recording
+ * Norms that run inside a GEMM's launch (fp32 models) count with it, in 0, 2
+ * or 5.  dllm_prof_enable(model, mask) starts recording
  * the kinds whose bit (1 << kind) is set and clears earlier records (mask 0
  * stops); dllm_prof_read waits for the recorded work and returns the summed
  * duration in milliseconds and the launch count of one kind.  Events are host

@@ -389,10 +389,11 @@ void run_layer_bf16(const dllm_model* m, int layer, int part, int B, int L, void
   }
 }
 
-// RMSNorm of rows (b, row0 + i), i < rows, of h into g.normed and the GEMM g on
-// them: one launch where the GEMM takes the norm along, else two.
-void norm_gemm_f32(const dllm_model* m, GemmF32 g, const float* h, const float* gain, float* normed, int B, int rows,
-                   int L, int row0, hipStream_t s, int kind) {
+// The GEMM g set up for the RMS-normalised rows (b, row0 + i), i < rows, of h, with
+// a copy of them at `normed`: it takes the norm along where it can, else the norm
+// is launched here.
+GemmF32 normed_gemm_f32(const dllm_model* m, GemmF32 g, const float* h, const float* gain, float* normed, int B,
+                        int rows, int L, int row0, hipStream_t s) {
   g.M = B * rows;
   g.K = m->cfg.d_model;
   g.A = h;
@@ -410,8 +411,7 @@ void norm_gemm_f32(const dllm_model* m, GemmF32 g, const float* h, const float* 
     g.gain = nullptr;
     g.normed = nullptr;
   }
-  ProfScope p(m, kind, s);
-  launch_gemm_f32(g, s);
+  return g;
 }
 
 void run_layer_f32(const dllm_model* m, int layer, int part, int B, int L, void* ws, const Layout& lay,
@@ -439,7 +439,11 @@ void run_layer_f32(const dllm_model* m, int layer, int part, int B, int L, void*
     g.Hq = c.n_heads;
     g.Hkv = c.n_kv_heads;
     g.hd = hd;
-    norm_gemm_f32(m, g, h, Wf(m, base + 0), at<float>(ws, lay.a_attn), B, Lq, Lq, 0, s, PK_QKV);
+    g = normed_gemm_f32(m, g, h, Wf(m, base + 0), at<float>(ws, lay.a_attn), B, Lq, Lq, 0, s);
+    {
+      ProfScope p(m, PK_QKV, s);
+      launch_gemm_f32(g, s);
+    }
     {
       ProfScope p(m, PK_ATTN, s);
       launch_attn_f32(g.q, g.k, g.vt, at<float>(ws, lay.attn), B, Lq, L, c.n_heads, c.n_kv_heads, hd, s);
@@ -462,7 +466,11 @@ void run_layer_f32(const dllm_model* m, int layer, int part, int B, int L, void*
     g.W0 = Wf(m, base + 6);
     g.W1 = Wf(m, base + 7);
     g.C = at<float>(ws, lay.u);
-    norm_gemm_f32(m, g, h, Wf(m, base + 5), at<float>(ws, lay.a_mlp), B, Lq, Lq, 0, s, PK_GATEUP);
+    g = normed_gemm_f32(m, g, h, Wf(m, base + 5), at<float>(ws, lay.a_mlp), B, Lq, Lq, 0, s);
+    {
+      ProfScope p(m, PK_GATEUP, s);
+      launch_gemm_f32(g, s);
+    }
     GemmF32 dn{};
     dn.epi = F32_RESID;
     dn.M = M;
@@ -532,7 +540,9 @@ void run_head_bufs(const dllm_model* m, int B, int L, int row0, int rows, float*
     g.N = c.vocab;
     g.W0 = Wf(m, 2 + 9 * nl);
     g.C = logits ? logits : hb.logits;
-    norm_gemm_f32(m, g, hb.h, Wf(m, 1 + 9 * nl), static_cast<float*>(hb.hb), B, rows, L, row0, s, PK_HEAD);
+    g = normed_gemm_f32(m, g, hb.h, Wf(m, 1 + 9 * nl), static_cast<float*>(hb.hb), B, rows, L, row0, s);
+    ProfScope p(m, PK_HEAD, s);
+    launch_gemm_f32(g, s);
     launch_vocab_reduce_f32(g.C, R, c.vocab, c.mask_id, conf, argmax, s);
   } else {
     {

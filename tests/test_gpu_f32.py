@@ -135,3 +135,21 @@ def test_queries_without_a_score_leave_the_others_alone(gpu_lib, hd):
         ref = (p / p.sum(-1, keepdims=True)) @ V[h // rep].T
         # float64 sums on both sides: what differs is one float32 rounding of values of size ~1
         np.testing.assert_allclose(out[h, good], ref, rtol=1e-6, atol=1e-6)
+
+
+def test_head_timing_holds_the_reduction(gpu_lib):
+    """PROF_HEAD is the head's GEMM and reduction: nearly all of a forward without layers over a wide vocabulary."""
+    cfg = synth.ModelConfig("f32-head", n_layers=0, d_model=16, n_heads=1, n_kv_heads=1, head_dim=64, d_ff=16,
+                            vocab=400000, rope_base=10000.0, dtype="f32")
+    model = B.Model(cfg, [t.cuda() for t in synth.make_weights(cfg, "cpu")])
+    x, ws = synth.make_ints((1, 1), 3, 0, cfg.vocab).cuda(), model.workspace(1, 1, 1)
+    model.forward(x, 0, 1, ws=ws)
+    a, b = torch.cuda.Event(True), torch.cuda.Event(True)
+    model.prof_enable([B.PROF_HEAD])
+    a.record()
+    for _ in range(10):
+        model.forward(x, 0, 1, ws=ws)
+    b.record()
+    b.synchronize()
+    ms, n = model.prof_read(B.PROF_HEAD)
+    assert n == 10 and ms > 0.5 * a.elapsed_time(b)
