@@ -128,10 +128,11 @@ void launch_embed(const int32_t* x, const void* E, int dtype, float* h, int B, i
 // RMSNorm of one row per 256-thread block.  The sum of squares is accumulated
 // in float64 in a fixed order (per-thread strided sums, then a fixed tree), so
 // results are run-to-run identical; scaling and the gain are applied in float32.
+// outf (at most GEMM_ROWS_MAX rows): a second copy in MFMA operand order.
 template <typename TG, typename TO>
 __global__ void __launch_bounds__(256) rmsnorm_kernel(const float* __restrict__ h, const TG* __restrict__ g,
-                                                      TO* __restrict__ out, int rows, int L, int row0, int d,
-                                                      float eps) {
+                                                      TO* __restrict__ out, TO* __restrict__ outf, int rows, int L,
+                                                      int row0, int d, float eps) {
   const int r = blockIdx.x;
   const int b = r / rows, i = r % rows;
   const float* src = h + ((size_t)b * L + row0 + i) * d;
@@ -148,7 +149,11 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(const float* __restrict__ 
   const double tot = (part[0] + part[1]) + (part[2] + part[3]);
   const float rstd = (float)(1.0 / sqrt(tot / (double)d + (double)eps));
   TO* dst = out + (size_t)r * d;
-  for (int c = threadIdx.x; c < d; c += 256) Act<TO>::store(dst, c, src[c] * rstd * Act<TG>::load(g, c));
+  for (int c = threadIdx.x; c < d; c += 256) {
+    const float y = src[c] * rstd * Act<TG>::load(g, c);
+    Act<TO>::store(dst, c, y);
+    if (outf) Act<TO>::store(outf, frag_at(((int)gridDim.x + 31) >> 5, r, c), y);
+  }
 }
 
 // Vector form of the same computation for d % 4 == 0 and d <= 1024 NV: the
@@ -206,7 +211,7 @@ void launch_rmsnorm_t(const float* h, const TG* g, TO* out, int B, int rows, int
     else
       hipLaunchKernelGGL((rmsnorm_vec_kernel<TG, TO, 8>), grid, blk, 0, s, h, g, out, rows, L, row0, d, eps);
   } else {
-    hipLaunchKernelGGL((rmsnorm_kernel<TG, TO>), grid, blk, 0, s, h, g, out, rows, L, row0, d, eps);
+    hipLaunchKernelGGL((rmsnorm_kernel<TG, TO>), grid, blk, 0, s, h, g, out, (TO*)nullptr, rows, L, row0, d, eps);
   }
 }
 
@@ -282,13 +287,20 @@ __global__ void __launch_bounds__(NT) resid_rmsnorm_kernel(float* __restrict__ h
 void launch_resid_rmsnorm(float* h, const PendingResid& pend, const bf16_t* g, bf16_t* out, bf16_t* outf, int M, int d,
                           float eps, hipStream_t s) {
   if (M == 0) return;
+  if (outf && (M > GEMM_ROWS_MAX || d % 16 != 0))
+    throw HipError("resid_rmsnorm: operand order holds 64 rows of whole slices");
+  // nothing pending, and a row or gain the kernel below does not take: the general norm
+  if (outf && pend.split == 0 && (d > 8192 || (uintptr_t)g % 16 != 0)) {
+    hipLaunchKernelGGL((rmsnorm_kernel<bf16_t, bf16_t>), dim3(M), dim3(256), 0, s, h, g, out, outf, M, M, 0, d, eps);
+    DLLM_LAUNCH_CHECK("rmsnorm");
+    return;
+  }
   if (d % 4 != 0 || d > 8192 ||
       ((uintptr_t)h | (uintptr_t)pend.part | (uintptr_t)g | (uintptr_t)out | (uintptr_t)outf) % 16 != 0)
     throw HipError("resid_rmsnorm: needs d % 4 == 0, d <= 8192 and 16-byte aligned rows");
   const long MN = (long)M * d;
   // the split count is a template parameter so that every partial's loads are in flight at once
   if (outf) {
-    if (M > GEMM_ROWS_MAX || d % 16 != 0) throw HipError("resid_rmsnorm: operand order holds 64 rows of whole slices");
     auto go = [&](auto nvc, auto sc) {
       hipLaunchKernelGGL((resid_rmsnorm_kernel<decltype(nvc)::value, decltype(sc)::value, 1024>), dim3(M), dim3(1024),
                          0, s, h, pend.part, MN, g, out, outf, d, eps);

@@ -117,7 +117,8 @@ void launch_gemm_bf16(const GemmArgs& a, hipStream_t s, PendingResid* defer = nu
 //   h[m, :] += sum_z part[z, m, :]   (z in order, as the split-K reduction does)
 //   out[m, :] = bf16(RMSNorm(h[m, :]) * g)
 // With outf (M <= GEMM_ROWS_MAX) the normed rows also go there in operand order;
-// such launches run one 1024-thread workgroup per row, and pend may be empty.
+// such launches run one 1024-thread workgroup per row, and pend may be empty:
+// then d and the alignment of g are free.
 void launch_resid_rmsnorm(float* h, const PendingResid& pend, const bf16_t* g, bf16_t* out, bf16_t* outf, int M, int d,
                           float eps, hipStream_t s);
 // Packed copy of a GEMM's virtual weight matrix (g's W0/W1/W2, n0, n1, N, K,

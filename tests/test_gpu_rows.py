@@ -43,6 +43,22 @@ def test_full_forward_of_few_rows(gpu_lib, shape, Bn, L):
     check_layer(model, cfg, w, ws, Bn, L, 0)
 
 
+@pytest.mark.parametrize("d,offset", [(8448, 0), (512, 1)])
+@pytest.mark.parametrize("Bn,L", [(1, 5), (2, 31)])
+def test_half_layers_of_wide_rows_and_of_gains_at_any_element(gpu_lib, d, offset, Bn, L):
+    """Rows beyond the vector norms' 8192 columns, and gains that are not 16-byte aligned."""
+    cfg = synth.ModelConfig("norm-edge", n_layers=1, d_model=d, n_heads=2, n_kv_heads=2, head_dim=128, d_ff=128,
+                            vocab=1000, rope_base=10000.0, dtype="bf16", norm_gain_std=0.1)
+    w = synth.make_weights(cfg, "cpu")
+    dev = [t.cuda() for t in w]
+    for i in (1, 6):  # the layer's two gains
+        dev[i] = torch.cat([dev[i][:offset], dev[i]])[offset:]
+    model = B.Model(cfg, dev).pack_weights()
+    ws = model.workspace(Bn, L, 0)
+    model.embed(synth.make_ints((Bn, L), 3, 0, cfg.vocab).cuda(), ws)
+    check_layer(model, cfg, [t.to(torch.float32).numpy() for t in w], ws, Bn, L, 0)
+
+
 @pytest.mark.parametrize("shape", SHAPES[1:])
 @pytest.mark.parametrize("Bn,L,row0,rows", [(1, 77, 40, 32), (1, 515, 483, 32), (16, 33, 0, 4), (3, 50, 9, 16), (1, 200, 101, 64), (2, 96, 64, 32)])
 def test_cached_rows(gpu_lib, shape, Bn, L, row0, rows):
