@@ -1818,7 +1818,8 @@ Plan plan(int M, int N, int K, int epi) {
       continue;
     const int max_split = M <= 128 ? 16 : 8;
     for (int split = 1; split <= max_split; ++split) {
-      if (split > 1 && ((epi != EPI_RESID && M > 128) || ksteps / split < 4)) break;
+      // the 256-row tiles' kernel has no partial sums but the residual's
+      if (split > 1 && ((epi != EPI_RESID && (M > 128 || c.bm == 256)) || ksteps / split < 4)) break;
       const long rounds = (tiles * split + 255) / 256;
       const double t_mma = (double)rounds * ((ksteps + split - 1) / split) * c.t_kstep_us;
       const double t_w = 2.0 * N * K / (W_BYTES_PER_US * std::min(1.0, (double)(tiles * split) / 256));
@@ -1849,6 +1850,7 @@ void launch_tile(const GemmArgs& g, int split, hipStream_t s) {
 
 template <class TL, int EPI>
 void launch_tile16(const GemmArgs& g, int split, hipStream_t s) {
+  if (EPI != EPI_RESID && split != 1) throw HipError("gemm16: a K split is for residual GEMMs");
   const int tiles = ((g.M + TL::BM - 1) / TL::BM) * (g.N / TL::BN);
   const size_t lds = lds_bytes16<TL, EPI>();
   static const hipError_t attr = hipFuncSetAttribute((const void*)gemm16_kernel<TL, EPI>,
