@@ -61,7 +61,8 @@ enum { DLLM_F32 = 0, DLLM_BF16 = 1 };
  * Requirements: n_heads % n_kv_heads == 0; 0 <= mask_id < vocab.
  * DLLM_BF16: head_dim == 128, d_model % 256 == 0, d_ff % 128 == 0, n_heads and
  * n_kv_heads even, no weight tensor over 2 GiB (a layer half with one is
- * refused when it is run: DLLM_EUNSUPPORTED).  DLLM_F32: head_dim in {64, 128}, sequence length <= 8000.
+ * refused when it is run: DLLM_EUNSUPPORTED).  DLLM_F32: head_dim in {64, 128},
+ * sequence length <= 8000 (the longest that is tested).
  */
 typedef struct dllm_model_cfg {
   int32_t n_layers, d_model, n_heads, n_kv_heads, head_dim, d_ff, vocab, mask_id;

@@ -155,6 +155,10 @@ T* at(void* ws, size_t off) {
   return reinterpret_cast<T*>(static_cast<char*>(ws) + off);
 }
 
+// The longest sequence of a float32 model that the interface promises and the
+// tests cover; no kernel's memory depends on it.
+constexpr int F32_MAX_LEN = 8000;
+
 void check_model(const dllm_model* m) { require(m != nullptr, DLLM_EINVAL, "model is NULL"); }
 
 void check_ws(const dllm_model* m, int B, int L, int rows, void* ws, size_t bytes, Layout* lay) {
@@ -164,7 +168,7 @@ void check_ws(const dllm_model* m, int B, int L, int rows, void* ws, size_t byte
   if (m->cfg.dtype == DLLM_BF16)
     require((long)B * rows <= head_bf16_max_rows(), DLLM_EUNSUPPORTED, "B * rows exceeds the LM-head kernel limit");
   else
-    require(L <= 8000, DLLM_EUNSUPPORTED, "float32 attention keeps all scores in LDS: L <= 8000");
+    require(L <= F32_MAX_LEN, DLLM_EUNSUPPORTED, "float32 models take sequences of at most 8000 positions");
   require(ws != nullptr, DLLM_EINVAL, "workspace is NULL");
   require(((uintptr_t)ws & 255) == 0, DLLM_EINVAL, "workspace must be 256-byte aligned");
   *lay = make_layout(m->cfg, B, L, rows);

@@ -137,6 +137,21 @@ def test_queries_without_a_score_leave_the_others_alone(gpu_lib, hd):
         np.testing.assert_allclose(out[h, good], ref, rtol=1e-6, atol=1e-6)
 
 
+@pytest.mark.parametrize("hd", [64, 128])
+def test_longest_sequence(gpu_lib, hd):
+    """A window at the end of 8000 positions; one more is refused."""
+    cfg = config(256, 4, 2, hd, 64, 64)
+    w, L, rows = synth.make_weights(cfg, "cpu"), 8000, 3
+    _, run = windowed(cfg, w, synth.make_ints((1, L), 3, 0, cfg.vocab), L - rows, rows)
+    q, K, V, out = run()
+    for h in range(cfg.n_heads):
+        sc = q[h] @ K[h // 2].T / math.sqrt(hd)
+        p = np.exp(sc - sc.max(-1, keepdims=True))
+        np.testing.assert_allclose(out[h], (p / p.sum(-1, keepdims=True)) @ V[h // 2].T, rtol=1e-6, atol=1e-6)
+    with pytest.raises(B.DllmError, match="8000"):
+        windowed(cfg, w, synth.make_ints((1, L + 1), 3, 0, cfg.vocab), L - rows, rows)
+
+
 def test_head_timing_holds_the_reduction(gpu_lib):
     """PROF_HEAD is the head's GEMM and reduction: nearly all of a forward without layers over a wide vocabulary."""
     cfg = synth.ModelConfig("f32-head", n_layers=0, d_model=16, n_heads=1, n_kv_heads=1, head_dim=64, d_ff=16,
