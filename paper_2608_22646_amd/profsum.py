@@ -79,7 +79,7 @@ def traffic(fetch, write, cfetch, cwrite, substr, copy_bytes, command):
 def util(path, cus, xcds, command):
     import collections
     import statistics
-    keys = ("gemm_wd_kernel", "gemm_bf16_kernel", "gemm_rows_kernel", "attn_", "head_")
+    keys = ("gemm_wd_kernel", "gemm_bf16_kernel", "gemm16_kernel", "gemm_rows_kernel", "gemm_f32_kernel", "attn_", "head_")
     per = collections.defaultdict(lambda: collections.defaultdict(list))
     dur = collections.defaultdict(dict)
     for r in csv.DictReader(open(path)):

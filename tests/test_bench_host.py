@@ -70,3 +70,22 @@ def test_profile_utilisation_summary(tmp_path, capsys):
     n, us, ghz, mf, ta, wt = row[0].split()[:6]
     assert (int(n), float(us), float(ghz)) == (2, 10.0, 2.0)
     assert (float(mf), float(ta), float(wt)) == (0.5, 0.75, 0.333)
+
+
+def test_profile_utilisation_covers_every_gemm_kernel(tmp_path, capsys):
+    """Every GEMM kernel of the sources gets a row."""
+    import glob
+    import re
+
+    from paper_2608_22646_amd import build, profsum
+    names = set()
+    for f in glob.glob(os.path.join(build.CSRC, "*.hip")):
+        names |= set(re.findall(r"^__global__ void[^;{]*?\b(gemm\w*_kernel)\(", open(f).read(), re.M))
+    assert {"gemm16_kernel", "gemm_wd_kernel"} <= names
+    counters = ("GRBM_GUI_ACTIVE", "SQ_VALU_MFMA_BUSY_CYCLES", "TA_TA_BUSY_sum", "SQ_WAIT_INST_ANY", "SQ_WAVE_CYCLES")
+    rows = [f'{d},"void dllm::{n}<X>(dllm::Args)",{k},1000,0,10000' for d, n in enumerate(sorted(names)) for k in counters]
+    path = tmp_path / "c.csv"
+    path.write_text("\n".join(["Dispatch_Id,Kernel_Name,Counter_Name,Counter_Value,Start_Timestamp,End_Timestamp"] + rows))
+    profsum.util(str(path), 256, 8, "cmd")
+    out = capsys.readouterr().out
+    assert all(n + "<X>" in out for n in names)
