@@ -28,9 +28,10 @@ def small():
     return B.Model(CFG, [t.cuda() for t in w]), [t.to(torch.float32).numpy() for t in w]
 
 
-# L = 33 .. 64: one streaming workgroup a head; 65 .. : the key-group kernel with
-# 64 and 96 queries; (16, 509) the four-wave and (4, 8201) the eight-wave streaming kernel
-@pytest.mark.parametrize("Bn,L", [(1, 33), (3, 63), (1, 65), (2, 101), (1, 515), (1, 2999), (16, 509), (4, 8201)])
+# L = 33 .. 64: one streaming workgroup a head; (1, 65) .. (1, 2999) the key-group kernel
+# with 64 queries a workgroup, (4, 1045) with 96; (16, 509) the four-wave and (4, 8201) the eight-wave streaming kernel
+@pytest.mark.parametrize("Bn,L", [(1, 33), (3, 63), (1, 65), (2, 101), (1, 515), (1, 2999), (4, 1045), (16, 509),
+                                  (4, 8201)])
 def test_full_layer(gpu_lib, small, Bn, L):
     model, w = small
     ws = model.workspace(Bn, L, 0)

@@ -32,9 +32,11 @@ def model_of(d, heads, kv, ff, layers=1):
 # (d, heads, kv heads, d_ff): 256 = eight groups, one 16-k slice per wave; 2304 =
 # 72 groups; d_ff 18944 = 1184 gate/up groups (five a workgroup at 32 rows)
 SHAPES = [(256, 2, 2, 128), (2304, 18, 2, 1408), (3584, 28, 4, 18944)]
+# q/k/v two groups a workgroup and gate/up three, and the other way round
+WIDE = [(512, 32, 32, 12288), (512, 48, 48, 8192)]
 
 
-@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("shape", SHAPES + WIDE)
 @pytest.mark.parametrize("Bn,L", [(1, 1), (1, 31), (2, 17), (1, 64)])
 def test_full_forward_of_few_rows(gpu_lib, shape, Bn, L):
     cfg, model, w = model_of(*shape)
