@@ -63,7 +63,7 @@ void launch_vocab_reduce_f32(const float* logits, int R, int V, int mask_id, flo
                              hipStream_t s);
 
 // ---- bf16 path -------------------------------------------------------------
-enum GemmEpi { EPI_QKV_ROPE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_STORE = 3 };
+enum GemmEpi { EPI_QKV_ROPE = 0, EPI_RESID = 1, EPI_SWIGLU = 2 };
 
 struct GemmArgs {
   int epi;
@@ -78,7 +78,7 @@ struct GemmArgs {
   int n0, n1;               // rows of W0 and W1 (QKV: Hq*hd, Hkv*hd)
   // epilogue targets
   float* resid;             // EPI_RESID: [M, N] float32, += result
-  bf16_t* out;              // EPI_SWIGLU: [M, N/2]; EPI_STORE: [M, N]
+  bf16_t* out;              // EPI_SWIGLU: [M, N/2]
   bf16_t* q; bf16_t* k; f16_t* vt;   // EPI_QKV_ROPE (v^T holds the bf16 values as IEEE half)
   const float* cosb; const float* sinb;
   // EPI_QKV_ROPE: row m = b Lq + i holds position pos0 + i of sequence b; q is
