@@ -31,8 +31,8 @@ typedef double f64x4_t __attribute__((ext_vector_type(4)));
 // launches and short k chains per wave.  The kernel this replaces (one float64
 // dot product per thread out of LDS, one launch per weight tensor, RoPE, SwiGLU
 // and the norms in launches of their own) took 9.8 us a launch at 96 rows and
-// 23 us at 948 (tiny model, 256 x 256); now 6.4-8.7 us for all of q/k/v or gate/up
-// with norm and epilogue at 96 rows, 20 / 30 us at 948 (22 TFLOP/s; 31 at 5840
+// 23 us at 948 (tiny model, 256 x 256); now 6.3 / 8.4 us for all of q/k/v / gate/up
+// with norm and epilogue at 96 rows, 19 / 30 us at 948 (22 TFLOP/s; 31 at 5840
 // rows, of the 54 a float64 library product reaches).
 //
 // With NORM the rows of A are RMS-normalised first, from the same registers
@@ -338,8 +338,8 @@ void launch_gemm_f32(GemmF32 g, hipStream_t s) {
 // stand the B operands of O^T += V^T P^T (slot g of MFMA r = key 4 g + r).  The
 // waves' (max, sum, output) states are merged in wave order through LDS.
 // One thread per key and per output dimension, scores in LDS, took 8.3 us at 96
-// tokens and 78 us at 4 x 237 (tiny model: 4 heads of 64); this kernel 8.5 and
-// 12.9 us (at 96 tokens its chain of loads, MFMAs and merge is all there is).
+// tokens and 78 us at 4 x 237 (tiny model: 4 heads of 64); this kernel 8.4 and
+// 12.6 us (at 96 tokens its chain of loads, MFMAs and merge is all there is).
 __device__ __forceinline__ float4 ld4u(const float* p) {  // 4-byte aligned
   float4 v;
   __builtin_memcpy(&v, p, 16);

@@ -558,11 +558,12 @@ __device__ __forceinline__ void epilogue_staged(const GemmArgs& g, char* lds, in
   staged_store<TL::BM, TL::BN, TL::NTH, EPI>(g, lds, m0, n0);
 }
 
-// Residual epilogue: h[m, n] += result, float32, 32 lanes on 128 contiguous bytes
-// of a row.  The values of h of a whole 32-row block are loaded before the first
-// is used: added four rows a round trip, output and down projections at 8192
-// rows of 4096 took 490 us on average, now 475 (458 with h never read; turned over
-// in LDS into 16-byte pieces 483: the memory's, not the address unit's, time).
+// Residual epilogue of the tiles of up to 128 rows without a K split: h[m, n] +=
+// result, float32, 32 lanes on 128 contiguous bytes of a row.  The values of h of a
+// whole 32-row block are loaded before the first is used.  Measured on the 256-row
+// tiles while they ran on this kernel (output and down projections at 8192 rows of
+// 4096, average): 490 us adding four rows a round trip, 475 so, 458 with h never
+// read, 483 turned over in LDS into 16-byte pieces.
 template <class TL>
 __device__ __forceinline__ void epilogue_resid(const GemmArgs& g, int wave, int lane, int m0, int n0,
                                                const f32x16_t (&acc)[TL::TI][TL::TJ]) {
@@ -747,8 +748,9 @@ __device__ __forceinline__ void stage_pair(const GemmArgs& g, char* lds, int ml,
 // now): gate/up 1349, 1214, 1187 us (1.39 PFLOP/s; a plain library product of that
 // shape 1092), q/k/v 716, 657, 639, output and down projections 465, 430, 419 on
 // average.  Dream-7B gate/up at 8448 rows 1944, 1752, 1693.  256 x 192, gate/up: 512
-// rows 107, 101, 97; 300 rows 97, 92, 88.  Matrix cores busy 69% of the cycles with two
-// slots, at 1.84 GHz; LDS moves 256 KiB a k-step, near its rate.
+// rows 107, 101, 97; 300 rows 97, 92, 88.  Matrix cores busy 73% of the cycles on
+// gate/up (69% with two slots), 67% on the others, at 1.87 GHz; LDS moves 256 KiB a
+// k-step, 91 bytes a cycle of its 128.
 // Four waves of 128 x 128 (a quarter less LDS traffic, one wave per SIMD): gate/up
 // 1186, the projections 415, q/k/v 656; Dream-7B 1721, 526 against 533, 288 against 270.
 // 16 x 16 x 32 in the register-direct kernel below changed nothing: its loads bound it.
@@ -1713,9 +1715,11 @@ __global__ void __launch_bounds__(256, 1) gemm_wd_kernel(GemmArgs g) {
 // Register-direct-weight plan for a launch of 129 .. 1024 rows with the packed
 // copy (tile 0: none, 1: WdWide, 2: WdKg2, 3: WdRes, 4: WdRes2, 5: WdQ2; split over K),
 // taken when the tile's workgroups fill at least 7/8 of the rounds they take
-// on the compute units.  At these sizes a workgroup is bounded by the bytes
-// its CU pulls through the vector-memory path, (BM + BN) x its k-range x 2
-// (the texture-address unit ~80% busy on the gate/up launch), so the time
+// on the compute units.  A workgroup's time follows the bytes its CU pulls
+// through the vector-memory path, (BM + BN) x its k-range x 2, though that path
+// is not full (texture-address unit 0.74 busy on the gate/up launch at 512 rows,
+// 0.50-0.66 on the others; matrix cores 0.58 and 0.22-0.44; the one wave of a SIMD
+// waits half of its cycles), so the time
 // model is rounds x (20.4 us per MB + 5 us), calibrated on the LLaDA-8B shape
 // at 512 rows (gate/up WdWide 85.6 us, q/k/v WdKg2 59.3, down WdRes at split 4
 // 54.9, output projection WdRes2 at split 2 26.1, down WdRes2 at split 2
@@ -1908,7 +1912,7 @@ size_t gemm_bf16_splitk_bytes(int M, int N, int K, int epi) {
   return b;
 }
 
-// resid += the S partials [S, MN], S = 1 .. 16
+// resid += the S partials [S, MN], S = 2 .. 16
 void launch_splitk(const float* part, float* resid, long MN, int split, hipStream_t s) {
   auto go = [&](auto sc) {
     hipLaunchKernelGGL(splitk_resid_kernel<decltype(sc)::value>, dim3(ceil_div(MN / 4, 256)), dim3(256), 0, s, part,
