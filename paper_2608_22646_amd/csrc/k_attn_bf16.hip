@@ -103,9 +103,9 @@ __device__ __forceinline__ float sum_pair32(float x) {
 // wave's softmax overlaps the other's MFMAs, and each K/V tile serves 256
 // queries).  K and V^T tiles are copied straight into a 3-stage LDS ring with
 // buffer_load_dwordx4 ... lds.  Keys past L are masked; their K rows read as
-// zero through the buffer bound, and their V^T columns hold either the next
-// d-row's (finite) values or, in the padding of a padded copy and past the end of
-// the head, zeros.  LV is the stride of V^T rows (a multiple of 8).  The 1/sqrt(hd)
+// zero through the buffer bound, and their V^T columns hold zeros in a padded copy
+// and past the end of the head, else the next d-row's (finite) values.  LV is the
+// stride of V^T rows (a multiple of 8; a padded copy's, of 64).  The 1/sqrt(hd)
 // * log2(e) scale is folded into the exp2 argument, and the running maximum is only raised when a tile's maximum
 // exceeds it by more than 8 (log2 units): unnormalised probabilities then stay
 // below 2^8 (exact to half's relative precision) and the O / l rescale is
@@ -959,9 +959,9 @@ __global__ void __launch_bounds__(64 * NWS, 1) attn_split_kernel(const bf16_t* _
 #endif
 }
 
-// vt rows of L values -> rows of LV = L rounded up to 8, the padding zero.  One
-// thread per eight values: a source row starts at any multiple of two bytes, so
-// the aligned dwords around them are loaded and shifted into place.
+// vt rows of L values -> rows of LV values, the padding zero.  One thread per eight
+// values: a source row starts at any multiple of two bytes, so the aligned dwords
+// around them are loaded and shifted into place.
 __global__ void __launch_bounds__(256) pad_vt_kernel(const f16_t* __restrict__ vt, f16_t* __restrict__ out, int rows,
                                                      int L, int LV) {
   const int per = LV / 8;
@@ -991,8 +991,13 @@ __global__ void __launch_bounds__(256) pad_vt_kernel(const f16_t* __restrict__ v
 
 }  // namespace
 
+// Stride of the V^T rows the streaming kernels read: L, or a padded copy's where L
+// is no multiple of 8 (rows of whole 64-key tiles, so that a row's last tile holds
+// zeros past L and nothing of the next row, whatever is there).
+inline int padded_len(int L) { return L % 8 ? (L + KT - 1) / KT * KT : L; }
+
 size_t attn_pad_bytes(int B, int Hkv, int L) {
-  return L % 8 ? (size_t)B * Hkv * HD * ((L + 7) / 8 * 8) * sizeof(f16_t) : 0;
+  return L % 8 ? (size_t)B * Hkv * HD * padded_len(L) * sizeof(f16_t) : 0;
 }
 
 size_t attn_split_bytes(int B, int Hq) { return (size_t)std::max(B * Hq, 512) * SPLIT_STATE; }
@@ -1031,7 +1036,7 @@ void launch_attn_bf16(const bf16_t* q, const bf16_t* k, const f16_t* vt, bf16_t*
   // V^T rows of whole 16-byte pieces: a padded copy where L is no multiple of 8
   // (the loads and stores of V once more, 5-6 us at 3 x 365 positions of 32 heads,
   // where reading the ragged rows element by element took the attention 56 us)
-  const int LV = (L + 7) / 8 * 8;
+  const int LV = padded_len(L);
   if (LV != L) {
     if (!pad) throw HipError("attn: lengths that are no multiple of 8 need the padded V^T buffer");
     const int rows = B * Hkv * HD;

@@ -49,3 +49,20 @@ def test_cached_window(gpu_lib, small, Bn, L, row0, rows):
     model.layer_kv(0, 2, Bn, L, 0, L, kv, ws)
     model.embed_rows(x.flip(1).contiguous(), row0, rows, ws)
     check_layer_cached(model, CFG, w, ws, kv, Bn, L, row0, rows, 0)
+
+
+@pytest.mark.parametrize("L,rows", [(45, 40), (203, 50)])  # a streaming workgroup a head; the key-group kernel
+def test_a_nan_value_stays_in_its_dimension(gpu_lib, small, L, rows):
+    """What lies behind a V^T row in the last tile takes no part, not even as 0 * NaN."""
+    model, _ = small
+    kv, ws = model.kv_cache(1, L), model.workspace(1, L, rows)
+    x = synth.make_ints((1, L), 4, 0, CFG.vocab).cuda()
+    model.embed(x, ws)
+    model.layer_kv(0, 2, 1, L, 0, L, kv, ws)
+    n = (2 * L * 128 * 2 + 255) // 256 * 256
+    kv[n:n + 2 * 128 * L * 2].view(torch.float16).view(2, 128, L)[:, 70, :5] = math.nan
+    model.embed_rows(x, L - rows, rows, ws)
+    model.layer_kv(0, 0, 1, L, L - rows, rows, kv, ws)
+    out = ws[model.layout(1, L, rows).attn:][:rows * 512 * 2].view(torch.bfloat16).view(rows, 4, 128)
+    nan = torch.isnan(out)
+    assert nan[:, :, 70].all() and int(nan.sum()) == rows * 4
